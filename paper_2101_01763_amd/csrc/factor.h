@@ -5,7 +5,6 @@
 #include <functional>
 #include <map>
 #include <memory>
-#include <initializer_list>
 #include <vector>
 
 #include "internal.h"
@@ -39,29 +38,67 @@ struct PullSet {
   int set(Factor &F, std::vector<PullGroup> G, const std::vector<PullItem> &I);
 };
 
-// batched GEMVs of one sweep step, split into bands of output rows; for
-// in-place use the union of output slots is copied back from scratch
+// batched GEMVs of one sweep step, split into bands of output rows
 struct GemvSet {
   GemvDesc *d_items = nullptr;
   GemvChunk *d_chunks = nullptr;
   int nchunks = 0;
   int n = 0;
-  int32_t *d_slots = nullptr;
-  int64_t nslots = 0;
-  int set(Factor &F, std::vector<GemvDesc> items, const std::vector<const std::vector<int32_t> *> &oslots,
-          int trans, int rows = 0);
+  int set(Factor &F, std::vector<GemvDesc> items, int trans, int rows = 0);
+};
+
+// one launch of k_level: clusters of a level >= 1
+struct LevelSet {
+  std::vector<LevelTask> tasks;      // host copies, empty once uploaded
+  std::vector<LevelItem> items;
+  LevelTask *d_tasks = nullptr;
+  LevelItem *d_items = nullptr;
+  int n = 0, tot = 0, m = 0, pre = 0, nt = 256;
+  void add(const void *M, int ldm, const int32_t *slots, int size, int row0, int nrows, int base,
+           const std::vector<LevelItem> &its);
 };
 
 inline int ld4(int n) { return (n + 3) & ~3; }
 
-// apply plan of one level (see Factor::apply)
+// One sweep over a level l >= 1: at most three launches (inputs' matrices,
+// couplings, own matrices), fewer where steps are fused (see level_sets)
+struct LevelSweep {
+  LevelSet a, pull, c;
+};
+
+// apply plan of one level (see Factor::sweeps)
 struct ApplyLevel {
+  // level 0
   GemvSet inv, invT;            // interiors: A_ss^-1
   GemvSet F, B, FT, BT;         // interfaces
   PullSet fw;    // x_n -= A_ns t_s          (groups: neighbours)
   PullSet bw;    // x_s -= A_sn x_n          (groups: interiors)
-  PullSet tfw;   // x_n -= A_sn^T x_s        (groups: neighbours)
-  PullSet tbw;   // t_s  = A_ns^T x_n        (groups: all interiors)
+  PullSet tfw;   // x_n -= A_sn^T t_s        (groups: neighbours)
+  PullSet tbw;   // x_s -= A_ns^T x_n        (groups: interiors)
+  // levels >= 1: forward and backward sweep, plain and transposed
+  LevelSweep fwd[2], bwd[2];
+};
+
+// host description of a level >= 1, from which its sweeps are planned
+struct LevelSource {
+  struct Interior {
+    const void *Ainv;
+    const int32_t *slots;
+    int n, ld, sys;
+  };
+  struct Interface {
+    const void *F, *B;
+    const int32_t *slots;
+    int m, ld, sys;
+  };
+  struct Coupling {             // interior s, interface n (indices into the lists)
+    int s, n;
+    const void *Ans, *Asn;      // m_n x n_s and n_s x m_n
+    int ldns, ldsn;
+  };
+  std::vector<Interior> ints;
+  std::vector<Interface> ifs;
+  std::vector<Coupling> cpl;    // ordered by (s, n)
 };
 
 struct RankStat {
@@ -193,8 +230,9 @@ struct Factor {
   int member_pull(int l, PullSet ApplyLevel::*which, const std::vector<PullGroup> &G,
                   const std::vector<PullItem> &I, const std::vector<int> &gs);
   int member_gemv(int l, GemvSet ApplyLevel::*which, const std::vector<GemvDesc> &gv,
-                  const std::vector<const std::vector<int32_t> *> &os, const std::vector<int> &gs,
-                  int trans);
+                  const std::vector<int> &gs, int trans);
+  int level_sets(int l, const LevelSource &src);
+  int level_plan(ApplyLevel &AL, const LevelSource &src);
   int dalloc(void **p, size_t bytes, bool keep);
   int dalloc_next(void **p, size_t bytes);
   void free_temp();
@@ -212,7 +250,7 @@ struct Factor {
   static UpPart part(const std::vector<D> &v, D **out) {
     return UpPart{v.data(), v.size() * sizeof(D), (void **)out};
   }
-  int upload_parts(std::initializer_list<UpPart> parts, bool keep);
+  int upload_parts(const std::vector<UpPart> &parts, bool keep);
   int upload_slots(const std::vector<int32_t> &v, int32_t **out);
   int upload_level_slots(LevelState &S);
   // Host work that only the apply needs (sweep descriptor sets): queued
@@ -230,8 +268,8 @@ struct Factor {
   void mark(int phase);
   void collect_events();
   int level0(const NDResult &nd, LevelState &S);
-  int eliminate_dense(int l, LevelState &S);
-  int sparsify(int l, const NDResult &nd, LevelState &S, LevelState &Nx);
+  int eliminate_dense(int l, LevelState &S, LevelSource &src);
+  int sparsify(int l, const NDResult &nd, LevelState &S, LevelState &Nx, LevelSource &src);
   int build(const spand_bsr_t &A, const spand_grid_t &g, const spand_opts_t &o,
             const Factor *sym = nullptr);
   int build_batch(const std::vector<BatchSystem> &sys, const spand_opts_t &o);

@@ -161,17 +161,12 @@ int Factor::member_pull(int l, PullSet ApplyLevel::*which, const std::vector<Pul
 }
 
 int Factor::member_gemv(int l, GemvSet ApplyLevel::*which, const std::vector<GemvDesc> &gv,
-                        const std::vector<const std::vector<int32_t> *> &os,
                         const std::vector<int> &gs, int trans) {
   if (members.empty()) return SPAND_OK;
   std::vector<std::vector<GemvDesc>> gm(members.size());
-  std::vector<std::vector<const std::vector<int32_t> *>> om(members.size());
-  for (size_t i = 0; i < gv.size(); ++i) {
-    gm[size_t(gs[i])].push_back(gv[i]);
-    om[size_t(gs[i])].push_back(os[i]);
-  }
+  for (size_t i = 0; i < gv.size(); ++i) gm[size_t(gs[i])].push_back(gv[i]);
   for (size_t m = 0; m < members.size(); ++m)
-    SP_TRY((members[m].lv[size_t(l)].*which).set(*this, gm[m], om[m], trans));
+    SP_TRY((members[m].lv[size_t(l)].*which).set(*this, gm[m], trans));
   return SPAND_OK;
 }
 
@@ -186,7 +181,7 @@ int Factor::upload(const std::vector<D> &v, D **out, bool keep) {
   return SPAND_OK;
 }
 
-int Factor::upload_parts(std::initializer_list<UpPart> parts, bool keep) {
+int Factor::upload_parts(const std::vector<UpPart> &parts, bool keep) {
   size_t tot = 0;
   for (const auto &q : parts) tot += (q.bytes + 255) & ~size_t(255);
   for (const auto &q : parts) *q.dst = nullptr;
@@ -1166,12 +1161,11 @@ int Factor::level0(const NDResult &nd, LevelState &S) {
       });
     };
     emit(off_e, by_e, 0, 0, false, &ApplyLevel::fw);    // x_n -= A_ns t_s
-    emit(off_f, by_f, 1, 0, false, &ApplyLevel::bw);    // x_s -= A_sn x_n
-    emit(off_e, by_e, 1, 1, false, &ApplyLevel::tfw);   // x_n -= A_sn^T x_s
-    emit(off_f, by_f, 0, 1, true, &ApplyLevel::tbw);    // t_s = A_ns^T x_n
+    emit(off_f, by_f, 1, 0, true, &ApplyLevel::bw);     // x_s -= A_sn x_n
+    emit(off_e, by_e, 1, 1, false, &ApplyLevel::tfw);   // x_n -= A_sn^T t_s
+    emit(off_f, by_f, 0, 1, true, &ApplyLevel::tbw);    // x_s -= A_ns^T x_n
     trace("pull sets", 0);
     std::vector<GemvDesc> gv;
-    std::vector<const std::vector<int32_t> *> os;
     std::vector<int> vs;
     for (int s : leaves) {
       GemvDesc d{};
@@ -1180,21 +1174,20 @@ int Factor::level0(const NDResult &nd, LevelState &S) {
       d.rows = d.cols = S.size[s];
       d.lda = ld4(S.size[s]);
       gv.push_back(d);
-      os.push_back(&S.slots[s]);
       vs.push_back(csys(0, s));
       acct(csys(0, s), double(S.size[s]) * S.size[s] * tsz * 2, 0.0);   // A_ss^-1: both sweeps
     }
     // band height of the sweep GEMVs: autotuned once per (precision, b)
-    defer([this, &AL, gv, os, vs]() -> int {
+    defer([this, &AL, gv, vs]() -> int {
       void *tin;
       SP_TRY(dalloc(&tin, size_t(N) * 8, false));
       SP_HIP(hipMemsetAsync(tin, 0, size_t(N) * 8, stream));
-      auto build_set = [&](int R, GemvSet &g) { return g.set(*this, gv, os, 0, R); };
+      auto build_set = [&](int R, GemvSet &g) { return g.set(*this, gv, 0, R); };
       SP_TRY(autotune_gemv(ft, bs, build_set, (double *)tin, d_tbuf, stream, &gemv_rows));
-      SP_TRY(AL.inv.set(*this, gv, os, 0));
-      SP_TRY(AL.invT.set(*this, gv, os, 1));
-      SP_TRY(member_gemv(0, &ApplyLevel::inv, gv, os, vs, 0));
-      return member_gemv(0, &ApplyLevel::invT, gv, os, vs, 1);
+      SP_TRY(AL.inv.set(*this, gv, 0));
+      SP_TRY(AL.invT.set(*this, gv, 1));
+      SP_TRY(member_gemv(0, &ApplyLevel::inv, gv, vs, 0));
+      return member_gemv(0, &ApplyLevel::invT, gv, vs, 1);
     });
     trace("inverse sweep sets", 0);
     for (int s : leaves)   // A_ns forward, A_sn backward; the inversion
@@ -1248,13 +1241,12 @@ int PullSet::set(Factor &F, std::vector<PullGroup> G, const std::vector<PullItem
   return SPAND_OK;
 }
 
-int GemvSet::set(Factor &F, std::vector<GemvDesc> items,
-                 const std::vector<const std::vector<int32_t> *> &oslots, int trans, int rows) {
+int GemvSet::set(Factor &F, std::vector<GemvDesc> items, int trans, int rows) {
   n = int(items.size());
   if (!n) return SPAND_OK;
-  int R = trans ? 256 : (rows > 0 ? rows : F.gemv_rows);
+  int R = trans ? GEMV_TROWS : (rows > 0 ? rows : F.gemv_rows);
   if (!trans && rows <= 0) {
-    // a set of fewer than 4096 bands (16 per CU: the upper levels) takes
+    // a set of fewer than 4096 bands (16 per CU: small systems) takes
     // shorter bands, down to one 16-row pass per workgroup: its launch is
     // bound by the passes' latency, not by bytes.  Each row's sum is the
     // same whatever the band.
@@ -1263,26 +1255,203 @@ int GemvSet::set(Factor &F, std::vector<GemvDesc> items,
     while (R > 16 && tot < int64_t(R) * 4096) R /= 2;
   }
   std::vector<GemvChunk> ch;
-  std::vector<int32_t> sl;
   for (int i = 0; i < n; ++i) {
     items[i].trans = trans;
     for (int r0 = 0; r0 < items[i].rows; r0 += R)
       ch.push_back(GemvChunk{i, r0, std::min(R, items[i].rows - r0), 0});
-    sl.insert(sl.end(), oslots[i]->begin(), oslots[i]->begin() + items[i].rows);
   }
   nchunks = int(ch.size());
-  nslots = int64_t(sl.size());
-  SP_TRY(F.upload_parts({Factor::part(items, &d_items), Factor::part(ch, &d_chunks),
-                         Factor::part(sl, &d_slots)},
-                        true));
+  SP_TRY(F.upload_parts({Factor::part(items, &d_items), Factor::part(ch, &d_chunks)}, true));
+  return SPAND_OK;
+}
+
+// ------------------------------------------------------------------ sweep plans of levels >= 1
+// One workgroup's task: items are cut into batches whose inputs fit the
+// staging buffers (by the items alone, so that a cluster's sums do not
+// depend on the launch it is part of).
+void LevelSet::add(const void *M, int ldm, const int32_t *slots, int size, int row0, int nrows,
+                   int base, const std::vector<LevelItem> &its) {
+  LevelTask t{};
+  t.M = M;
+  t.ldm = ldm;
+  t.slots = slots;
+  t.m = size;
+  t.row0 = row0;
+  t.nrows = nrows;
+  t.base = base;
+  t.item_begin = int(items.size());
+  size_t first = 0;
+  int off = 0;
+  for (size_t i = 0; i < its.size(); ++i) {
+    LevelItem it = its[i];
+    if (i > first && (off + it.k > LEVEL_CAP || int(i - first) == LEVEL_MAXIT)) {
+      items[size_t(t.item_begin) + first].nb = int(i - first);
+      first = i;
+      off = 0;
+    }
+    it.off = off;
+    off += it.k;
+    tot = std::max(tot, off);
+    pre = pre || it.P;
+    items.push_back(it);
+  }
+  if (!its.empty()) items[size_t(t.item_begin) + first].nb = int(its.size() - first);
+  t.item_end = int(items.size());
+  m = std::max(m, size);
+  tasks.push_back(t);
+  n = int(tasks.size());
+}
+
+// The sweeps over one level: V is the vector that holds the level's unknowns
+// (x at even levels, the scratch vector at odd ones), O the other one.
+//   forward   t_s = A_ss^-1 x_s        (V -> O)
+//             y_n = x_n - sum A_ns t_s
+//             O_n = F_n y_n
+//   backward  w_n = B_n O_n            (O -> V)
+//             y_s = x_s - sum A_sn w_n (to O where it is a launch of its own)
+//             V_s = A_ss^-1 y_s
+// (transposed: A_ss^-T, A_sn^T, B_n^T and F_n^T, A_ns^T, A_ss^-T.)
+// Three ways to launch a sweep: every step a launch of its own, rows cut
+// into bands (a); couplings and own matrix in one workgroup per cluster (b);
+// and the neighbours' products of the first step recomputed in the same
+// workgroup (c).  One launch costs about 5 us whatever it does, and one
+// compute unit draws about 100 GB/s, so the choice goes by the largest
+// matrix of the level and the number of clusters (apply in us at 128x128
+// p = 2 FP32, 96x96 p = 2 FP32 eps = 1e-3, 160x120 p = 1 FP32):
+//   all (a)          866, 672, 610
+//   all (b)          880, 683, 573
+//   all (c)          878, 714, 551
+//   the rules below  860, 681, 543
+// (c) pays while the repeated matrices are small (up to 64 KB, 128 unknowns
+// in FP32) and the level has too few clusters to fill the device; beyond
+// 256 KB a cluster per workgroup loses to bands of rows.  Workgroups of 1024
+// threads where the clusters do not fill the device (256 threads: 1020 us
+// instead of 860).
+int Factor::level_plan(ApplyLevel &AL, const LevelSource &src) {
+  const size_t tsz = fsize(ft);
+  size_t big = 0;
+  for (const auto &i : src.ifs) big = std::max(big, size_t(i.m) * i.m * tsz);
+  for (const auto &i : src.ints) big = std::max(big, size_t(i.n) * i.n * tsz);
+  const int nf = int(src.ifs.size()), ns = int(src.ints.size());
+  const bool fuse = big <= (size_t(256) << 10), small = big <= (size_t(64) << 10);
+  const bool redf = small && nf <= 512, redb = small && nf + ns <= 512;
+  std::vector<std::vector<const LevelSource::Coupling *>> byn(nf), bys(ns);
+  for (const auto &c : src.cpl) {
+    byn[c.n].push_back(&c);
+    bys[c.s].push_back(&c);
+  }
+  // rows of a band: 32 (16: 4079 us instead of 3876 at 256x256 p = 3; 64:
+  // 966 instead of 866 at 128x128 p = 2)
+  constexpr int band = 32;
+  auto banded = [&](LevelSet &L, const void *M, int ldm, const int32_t *slots, int size, int base,
+                    const std::vector<LevelItem> &its) {
+    for (int r0 = 0; r0 < size; r0 += band)
+      L.add(M, ldm, slots, size, r0, std::min(band, size - r0), base, its);
+  };
+  for (int tr = 0; tr < 2; ++tr) {
+    LevelSweep &fw = AL.fwd[tr], &bw = AL.bwd[tr];
+    // forward
+    if (!src.cpl.empty() && !redf)
+      for (const auto &i : src.ints) banded(fw.a, i.Ainv, i.ld, i.slots, i.n, 0, {});
+    for (int n = 0; n < nf; ++n) {
+      const auto &f = src.ifs[n];
+      std::vector<LevelItem> its;
+      for (const auto *c : byn[n]) {
+        const auto &s = src.ints[c->s];
+        LevelItem it{};
+        it.P = redf ? s.Ainv : nullptr;
+        it.ldp = s.ld;
+        it.B = tr ? c->Asn : c->Ans;
+        it.ldb = tr ? c->ldsn : c->ldns;
+        it.islot = s.slots;
+        it.k = s.n;
+        its.push_back(it);
+      }
+      const void *M = tr ? f.B : f.F;
+      if (fuse) {
+        fw.c.add(M, f.ld, f.slots, f.m, 0, f.m, 0, its);
+      } else {
+        if (!its.empty()) banded(fw.pull, nullptr, 0, f.slots, f.m, 0, its);
+        banded(fw.c, M, f.ld, f.slots, f.m, 0, {});
+      }
+    }
+    // backward
+    if (!redb)
+      for (const auto &f : src.ifs) banded(bw.a, tr ? f.F : f.B, f.ld, f.slots, f.m, 0, {});
+    else
+      for (const auto &f : src.ifs) bw.c.add(tr ? f.F : f.B, f.ld, f.slots, f.m, 0, f.m, 1, {});
+    for (int s = 0; s < ns; ++s) {
+      const auto &i = src.ints[s];
+      std::vector<LevelItem> its;
+      for (const auto *c : bys[s]) {
+        const auto &f = src.ifs[c->n];
+        LevelItem it{};
+        it.P = redb ? (tr ? f.F : f.B) : nullptr;
+        it.ldp = f.ld;
+        it.B = tr ? c->Ans : c->Asn;
+        it.ldb = tr ? c->ldns : c->ldsn;
+        it.islot = f.slots;
+        it.k = f.m;
+        its.push_back(it);
+      }
+      if (fuse) {
+        bw.c.add(i.Ainv, i.ld, i.slots, i.n, 0, i.n, 0, its);
+      } else {
+        banded(bw.pull, nullptr, 0, i.slots, i.n, 0, its);
+        banded(bw.c, i.Ainv, i.ld, i.slots, i.n, 0, {});
+      }
+    }
+    for (LevelSet *L : {&fw.a, &fw.pull, &fw.c, &bw.a, &bw.pull, &bw.c})
+      L->nt = fuse && (L == &fw.c || L == &bw.c) && L->n <= 1024 ? 1024 : 256;
+  }
+  std::vector<UpPart> up;
+  for (int tr = 0; tr < 2; ++tr)
+    for (LevelSweep *w : {&AL.fwd[tr], &AL.bwd[tr]})
+      for (LevelSet *L : {&w->a, &w->pull, &w->c}) {
+        up.push_back(part(L->tasks, &L->d_tasks));
+        up.push_back(part(L->items, &L->d_items));
+      }
+  SP_TRY(upload_parts(up, true));
+  for (int tr = 0; tr < 2; ++tr)
+    for (LevelSweep *w : {&AL.fwd[tr], &AL.bwd[tr]})
+      for (LevelSet *L : {&w->a, &w->pull, &w->c}) {
+        std::vector<LevelTask>().swap(L->tasks);
+        std::vector<LevelItem>().swap(L->items);
+      }
+  return SPAND_OK;
+}
+
+// every system's sweeps of a level, from the description of all its clusters
+int Factor::level_sets(int l, const LevelSource &src) {
+  SP_TRY(level_plan(lv[size_t(l)], src));
+  if (members.empty()) return SPAND_OK;
+  std::vector<LevelSource> ms(members.size());
+  std::vector<int> is(src.ints.size()), fs(src.ifs.size());
+  for (size_t q = 0; q < src.ints.size(); ++q) {
+    auto &v = ms[size_t(src.ints[q].sys)].ints;
+    is[q] = int(v.size());
+    v.push_back(src.ints[q]);
+  }
+  for (size_t q = 0; q < src.ifs.size(); ++q) {
+    auto &v = ms[size_t(src.ifs[q].sys)].ifs;
+    fs[q] = int(v.size());
+    v.push_back(src.ifs[q]);
+  }
+  for (auto c : src.cpl) {
+    auto &v = ms[size_t(src.ints[size_t(c.s)].sys)].cpl;
+    c.s = is[size_t(c.s)];
+    c.n = fs[size_t(c.n)];
+    v.push_back(c);
+  }
+  for (size_t m = 0; m < members.size(); ++m)
+    SP_TRY(level_plan(members[m].lv[size_t(l)], ms[m]));
   return SPAND_OK;
 }
 
 // ------------------------------------------------------------------ dense interior elimination (l >= 1)
-int Factor::eliminate_dense(int l, LevelState &S) {
+int Factor::eliminate_dense(int l, LevelState &S, LevelSource &src) {
   const size_t tsz = fsize(ft);
   const int ncl = int(S.size.size());
-  ApplyLevel &AL = lv[l];
   std::vector<int> ints;
   for (int c = 0; c < ncl; ++c)
     if (S.interior[c] && S.size[c] > 0) ints.push_back(c);
@@ -1441,142 +1610,22 @@ int Factor::eliminate_dense(int l, LevelState &S) {
     SP_TRY(gemm_batch(gm));
     trace("gemm", l);
   }
-  // apply descriptors
-  std::vector<GemvDesc> gv;
-  std::vector<const std::vector<int32_t> *> os;
-  std::vector<int> vs;
+  // the level's interiors and couplings, for its sweeps (the interfaces are
+  // numbered by cluster until sparsify lists them)
   for (int s : ints) {
-    GemvDesc d{};
-    d.A = Ainv[s];
-    d.islot = d.oslot = S.d_slots[s];
-    d.rows = d.cols = S.size[s];
-    d.lda = ld4(S.size[s]);
-    gv.push_back(d);
-    os.push_back(&S.slots[s]);
-    vs.push_back(csys(l, s));
-  }
-  defer([this, &AL, gv, os, vs, l]() {
-    SP_TRY(AL.inv.set(*this, gv, os, 0));
-    return member_gemv(l, &ApplyLevel::inv, gv, os, vs, 0);
-  });
-  defer([this, &AL, gv, os, vs, l]() {
-    SP_TRY(AL.invT.set(*this, gv, os, 1));
-    return member_gemv(l, &ApplyLevel::invT, gv, os, vs, 1);
-  });
-  std::vector<std::vector<PullItem>> fw(ncl), tfw(ncl);   // by neighbour n
-  std::vector<PullGroup> G;
-  std::vector<PullItem> I;
-  std::vector<PullGroup> G2;
-  std::vector<PullItem> I2;
-  for (int s : ints)
     for (size_t i = 0; i < nb[s].size(); ++i) {
       const int n = nb[s][i];
       const Blk &Ans = *Bns[s][i];   // |n| x |s|
       const Blk &Asn = *Bsn[s][i];   // |s| x |n|
-      PullItem p{};
-      p.B = Ans.p;
-      p.islot = S.d_slots[s];
-      p.rows = S.size[n];
-      p.cols = S.size[s];
-      p.ldb = Ans.cols;
-      p.trans = 0;
-      fw[n].push_back(p);
-      PullItem q{};
-      q.B = Asn.p;
-      q.islot = S.d_slots[s];
-      q.rows = S.size[n];
-      q.cols = S.size[s];
-      q.ldb = Asn.cols;
-      q.trans = 1;
-      tfw[n].push_back(q);
-      acct(csys(l, s), double(Ans.rows) * Ans.cols * tsz + double(Asn.rows) * Asn.cols * tsz, 0.0);
       if (S.size[n] > PULL_MAXR || S.size[s] > GEMV_MAXC) {
         set_error("coupling block %dx%d exceeds the sweep kernel limit", S.size[n], S.size[s]);
         return SPAND_EINVAL;
       }
+      src.cpl.push_back({int(src.ints.size()), n, Ans.p, Asn.p, Ans.cols, Asn.cols});
+      acct(csys(l, s), double(Ans.rows) * Ans.cols * tsz + double(Asn.rows) * Asn.cols * tsz, 0.0);
     }
-  std::vector<int> gs, gs2;
-  for (int n = 0; n < ncl; ++n) {
-    if (fw[n].empty()) continue;
-    PullGroup g{};
-    g.oslot = S.d_slots[n];
-    g.rows = S.size[n];
-    g.item_begin = int(I.size());
-    I.insert(I.end(), fw[n].begin(), fw[n].end());
-    g.item_end = int(I.size());
-    G.push_back(g);
-    gs.push_back(csys(l, n));
+    src.ints.push_back({Ainv[s], S.d_slots[s], S.size[s], ld4(S.size[s]), csys(l, s)});
   }
-  defer([this, &AL, G, I, gs, l]() {
-    SP_TRY(AL.fw.set(*this, G, I));
-    return member_pull(l, &ApplyLevel::fw, G, I, gs);
-  });
-  G.clear();
-  I.clear();
-  gs.clear();
-  for (int n = 0; n < ncl; ++n) {
-    if (tfw[n].empty()) continue;
-    PullGroup g{};
-    g.oslot = S.d_slots[n];
-    g.rows = S.size[n];
-    g.item_begin = int(I.size());
-    I.insert(I.end(), tfw[n].begin(), tfw[n].end());
-    g.item_end = int(I.size());
-    G.push_back(g);
-    gs.push_back(csys(l, n));
-  }
-  defer([this, &AL, G, I, gs, l]() {
-    SP_TRY(AL.tfw.set(*this, G, I));
-    return member_pull(l, &ApplyLevel::tfw, G, I, gs);
-  });
-  G.clear();
-  I.clear();
-  gs.clear();
-  for (int s : ints) {
-    PullGroup g{}, g2{};
-    g.oslot = g2.oslot = S.d_slots[s];
-    g.rows = g2.rows = S.size[s];
-    g.item_begin = int(I.size());
-    g2.item_begin = int(I2.size());
-    for (size_t i = 0; i < nb[s].size(); ++i) {
-      const int n = nb[s][i];
-      const Blk &Asn = *Bsn[s][i];
-      const Blk &Ans = *Bns[s][i];
-      PullItem p{};
-      p.B = Asn.p;
-      p.islot = S.d_slots[n];
-      p.rows = S.size[s];
-      p.cols = S.size[n];
-      p.ldb = Asn.cols;
-      p.trans = 0;
-      I.push_back(p);
-      PullItem q{};
-      q.B = Ans.p;
-      q.islot = S.d_slots[n];
-      q.rows = S.size[s];
-      q.cols = S.size[n];
-      q.ldb = Ans.cols;
-      q.trans = 1;
-      I2.push_back(q);
-    }
-    g.item_end = int(I.size());
-    g2.item_end = int(I2.size());
-    if (g.item_end > g.item_begin) {
-      G.push_back(g);
-      gs.push_back(csys(l, s));
-    }
-    G2.push_back(g2);
-    gs2.push_back(csys(l, s));
-  }
-  defer([this, &AL, G, I, gs, l]() {
-    SP_TRY(AL.bw.set(*this, G, I));
-    return member_pull(l, &ApplyLevel::bw, G, I, gs);
-  });
-  trace("sweep sets", l);
-  defer([this, &AL, G2, I2, gs2, l]() {
-    SP_TRY(AL.tbw.set(*this, G2, I2));
-    return member_pull(l, &ApplyLevel::tbw, G2, I2, gs2);
-  });
   // eliminated clusters leave the trailing matrix
   for (int s : ints) {
     for (int n : nb[s]) {
@@ -1590,7 +1639,7 @@ int Factor::eliminate_dense(int l, LevelState &S) {
 }
 
 // ------------------------------------------------------------------ interfaces (any level < top)
-int Factor::sparsify(int l, const NDResult &nd, LevelState &S, LevelState &Nx) {
+int Factor::sparsify(int l, const NDResult &nd, LevelState &S, LevelState &Nx, LevelSource &src) {
   const size_t tsz = fsize(ft);
   const int ncl = int(S.size.size());
   ApplyLevel &AL = lv[l];
@@ -1959,9 +2008,9 @@ int Factor::sparsify(int l, const NDResult &nd, LevelState &S, LevelState &Nx) {
   mark(PH_COMPRESS);
   {
     std::vector<GemmDesc> gm;
-    std::vector<GemvDesc> gf, gb;
-    std::vector<const std::vector<int32_t> *> os;
+    std::vector<GemvDesc> gf, gb;    // level 0
     std::vector<int> vs;
+    std::vector<int> fid(ncl, -1);   // levels >= 1: interface number of a cluster
     for (int s : ifs) {
       const int m = S.size[s];
       void *Fp, *Bp;
@@ -1987,30 +2036,40 @@ int Factor::sparsify(int l, const NDResult &nd, LevelState &S, LevelState &Nx) {
       h.alpha = 1.0;
       h.tri = GEMM_TRI_A_UPPER;   // Uh^-1 is upper triangular
       gm.push_back(h);
-      GemvDesc d{};
-      d.islot = d.oslot = S.d_slots[s];
-      d.rows = d.cols = m;
-      d.lda = ld4(m);
-      d.A = Fp;
-      gf.push_back(d);
-      d.A = Bp;
-      gb.push_back(d);
-      os.push_back(&S.slots[s]);
-      vs.push_back(csys(l, s));
+      if (l == 0) {
+        GemvDesc d{};
+        d.islot = d.oslot = S.d_slots[s];
+        d.rows = d.cols = m;
+        d.lda = ld4(m);
+        d.A = Fp;
+        gf.push_back(d);
+        d.A = Bp;
+        gb.push_back(d);
+        vs.push_back(csys(l, s));
+      } else {
+        fid[s] = int(src.ifs.size());
+        src.ifs.push_back({Fp, Bp, S.d_slots[s], m, ld4(m), csys(l, s)});
+      }
       acct(csys(l, s), 2.0 * double(m) * m * tsz, 4.0 * double(m) * m * m);   // F_s forward, B_s backward
     }
     SP_TRY(gemm_batch(gm));
     trace("gemm", l);
-    defer([this, &AL, gf, gb, os, vs, l]() {
-      SP_TRY(AL.F.set(*this, gf, os, 0));
-      SP_TRY(AL.B.set(*this, gb, os, 0));
-      SP_TRY(AL.FT.set(*this, gf, os, 1));
-      SP_TRY(AL.BT.set(*this, gb, os, 1));
-      SP_TRY(member_gemv(l, &ApplyLevel::F, gf, os, vs, 0));
-      SP_TRY(member_gemv(l, &ApplyLevel::B, gb, os, vs, 0));
-      SP_TRY(member_gemv(l, &ApplyLevel::FT, gf, os, vs, 1));
-      return member_gemv(l, &ApplyLevel::BT, gb, os, vs, 1);
-    });
+    if (l == 0) {
+      defer([this, &AL, gf, gb, vs]() {
+        SP_TRY(AL.F.set(*this, gf, 0));
+        SP_TRY(AL.B.set(*this, gb, 0));
+        SP_TRY(AL.FT.set(*this, gf, 1));
+        SP_TRY(AL.BT.set(*this, gb, 1));
+        SP_TRY(member_gemv(0, &ApplyLevel::F, gf, vs, 0));
+        SP_TRY(member_gemv(0, &ApplyLevel::B, gb, vs, 0));
+        SP_TRY(member_gemv(0, &ApplyLevel::FT, gf, vs, 1));
+        return member_gemv(0, &ApplyLevel::BT, gb, vs, 1);
+      });
+    } else {
+      for (auto &c : src.cpl) c.n = fid[c.n];
+      defer([this, l, src = std::move(src)]() { return level_sets(l, src); });
+      src = LevelSource{};
+    }
     trace("compress F/B sets", l);
   }
   // ---- merge: next-level clusters from the coarse parts
@@ -2303,22 +2362,23 @@ int Factor::numeric() {
   auto t1 = std::chrono::steady_clock::now();
   t_host_ms += std::chrono::duration<double, std::milli>(t1 - build_t0).count();
   mark(PH_GATHER);
-  LevelState S, prev;   // prev: the level before, read by sweep sets not yet built
+  LevelState S;
   SP_TRY(level0(nd, S));
   for (int l = 0; l < L; ++l) {
-    if (l >= 1) SP_TRY(eliminate_dense(l, S));
+    LevelSource src;
+    if (l >= 1) SP_TRY(eliminate_dense(l, S, src));
     // a system whose top level this is keeps what its top clusters hold
     for (size_t m = 0; m < members.size(); ++m)
       if (members[m].L - 1 == l)
         for (int c = 0; c < int(S.size.size()); ++c)
           if (csys(l, c) == int(m)) members[m].top_size += S.size[c];
-    if (l == L - 1) break;
+    if (l == L - 1) {
+      if (l >= 1) SP_TRY(level_sets(l, src));
+      break;
+    }
     LevelState Nx;
-    SP_TRY(sparsify(l, nd, S, Nx));
+    SP_TRY(sparsify(l, nd, S, Nx, src));
     free_temp();
-    // every set that read the level before was built in this sparsify (at
-    // its rank read-back); the sets of this level's compression read S
-    prev = std::move(S);
     S = std::move(Nx);
   }
   int tops = 0;
@@ -2351,43 +2411,52 @@ int Factor::numeric() {
 // y = M^-1 r:  forward over levels applies L' (interiors: x_n -= A_ns A_ss^-1 x_s)
 // and F_s (interfaces); backward applies B_s and R' (x_s = A_ss^-1 (x_s - A_sn x_n)).
 // y = M^-T r:  forward applies R'^T and B_s^T, backward F_s^T and L'^T.
+// A level's unknowns live in x (even levels) or d_tbuf (odd levels): every
+// step reads one vector and writes the other, so that nothing is copied back
+// and the backward sweep finds the interiors' forward values untouched.
 int Factor::sweeps(const std::vector<ApplyLevel> &lv, double *x, int transpose, hipStream_t st) {
   const int L = int(lv.size());
-  auto inplace = [&](const GemvSet &g) -> int {
-    if (!g.n) return SPAND_OK;
-    SP_TRY(launch_gemv(ft, g.d_items, g.d_chunks, g.nchunks, x, d_tbuf, 1.0, 0.0, st));
-    return launch_slot_copy(g.d_slots, g.nslots, d_tbuf, x, st);
+  double *V[2] = {x, d_tbuf};
+  auto gemv = [&](const GemvSet &g, const double *in, double *out) {
+    return g.n ? launch_gemv(ft, g.d_items, g.d_chunks, g.nchunks, in, out, st) : SPAND_OK;
   };
-  if (!transpose) {
-    for (int l = 0; l < L; ++l) {
-      const ApplyLevel &A = lv[l];
-      if (A.fw.n) {
-        SP_TRY(launch_gemv(ft, A.inv.d_items, A.inv.d_chunks, A.inv.nchunks, x, d_tbuf, 1.0, 0.0, st));
-        SP_TRY(launch_pull2(ft, A.fw.d_groups, A.fw.d_items, A.fw.d_chunks, A.fw.nchunks, A.fw.trans, d_tbuf, x, -1.0, 1.0, st));
-      }
-      SP_TRY(inplace(A.F));
+  auto pull = [&](const PullSet &p, const double *in, const double *base, double *out) {
+    return p.n ? launch_pull2(ft, p.d_groups, p.d_items, p.d_chunks, p.nchunks, p.trans, in, base,
+                              out, -1.0, st)
+               : SPAND_OK;
+  };
+  auto level = [&](const LevelSet &s, const double *in, const double *b0, const double *b1, double *out) {
+    return launch_level(ft, transpose, s.d_tasks, s.n, s.d_items, s.tot, s.m, s.pre, s.nt, in, b0,
+                        b1, out, st);
+  };
+  if (L > 0) {
+    const ApplyLevel &A = lv[0];
+    const PullSet &fw = transpose ? A.tfw : A.fw;
+    if (fw.n) {
+      SP_TRY(gemv(transpose ? A.invT : A.inv, V[0], V[1]));
+      SP_TRY(pull(fw, V[1], V[0], V[0]));
     }
-    for (int l = L - 1; l >= 0; --l) {
-      const ApplyLevel &A = lv[l];
-      SP_TRY(inplace(A.B));
-      if (A.bw.n) SP_TRY(launch_pull2(ft, A.bw.d_groups, A.bw.d_items, A.bw.d_chunks, A.bw.nchunks, A.bw.trans, x, x, -1.0, 1.0, st));
-      SP_TRY(inplace(A.inv));
-    }
-  } else {
-    for (int l = 0; l < L; ++l) {
-      const ApplyLevel &A = lv[l];
-      SP_TRY(inplace(A.invT));
-      if (A.tfw.n) SP_TRY(launch_pull2(ft, A.tfw.d_groups, A.tfw.d_items, A.tfw.d_chunks, A.tfw.nchunks, A.tfw.trans, x, x, -1.0, 1.0, st));
-      SP_TRY(inplace(A.BT));
-    }
-    for (int l = L - 1; l >= 0; --l) {
-      const ApplyLevel &A = lv[l];
-      SP_TRY(inplace(A.FT));
-      if (A.tbw.n && A.invT.n) {
-        SP_TRY(launch_pull2(ft, A.tbw.d_groups, A.tbw.d_items, A.tbw.d_chunks, A.tbw.nchunks, A.tbw.trans, x, d_tbuf, 1.0, 0.0, st));
-        SP_TRY(launch_gemv(ft, A.invT.d_items, A.invT.d_chunks, A.invT.nchunks, d_tbuf, x, -1.0, 1.0, st));
-      }
-    }
+    SP_TRY(gemv(transpose ? A.BT : A.F, V[0], V[1]));
+  }
+  for (int l = 1; l < L; ++l) {
+    const LevelSweep &w = lv[l].fwd[transpose];
+    double *v = V[l & 1], *o = V[1 - (l & 1)];
+    SP_TRY(level(w.a, nullptr, v, nullptr, o));
+    SP_TRY(level(w.pull, o, v, nullptr, v));
+    SP_TRY(level(w.c, w.c.pre ? v : o, v, nullptr, o));
+  }
+  for (int l = L - 1; l >= 1; --l) {
+    const LevelSweep &w = lv[l].bwd[transpose];
+    double *v = V[l & 1], *o = V[1 - (l & 1)];
+    SP_TRY(level(w.a, nullptr, o, nullptr, v));
+    SP_TRY(level(w.pull, v, v, nullptr, o));
+    SP_TRY(level(w.c, w.c.pre ? o : v, w.pull.n ? o : v, o, v));
+  }
+  if (L > 0) {
+    const ApplyLevel &A = lv[0];
+    SP_TRY(gemv(transpose ? A.FT : A.B, V[1], V[0]));
+    SP_TRY(pull(transpose ? A.tbw : A.bw, V[0], V[0], V[1]));
+    SP_TRY(gemv(transpose ? A.invT : A.inv, V[1], V[0]));
   }
   return SPAND_OK;
 }

@@ -146,7 +146,7 @@ struct ElimDesc {
 };
 
 // Dense GEMV with gather/scatter through slot lists:
-// out[oslot[r]] = beta*out[oslot[r]] + alpha * sum_c op(A)(r,c) * in[islot[c]]
+// out[oslot[r]] = sum_c op(A)(r,c) * in[islot[c]]
 struct GemvDesc {
   const void *A;
   const int32_t *islot;
@@ -160,7 +160,29 @@ struct GemvChunk {
   int32_t item, row0, nrows, pad;
 };
 
-// Pull group: out[oslot[r]] += alpha * sum_items op(B_i) in[islot_i[c]].
+// One cluster of a sweep over a level l >= 1 (k_level): of its m unknowns
+//   y = base - sum_items op(B_i) (op(P_i) in_i)      (P_i null: in_i itself)
+//   out[rows row0 .. row0+nrows) = op(M) y           (M null: y)
+// with all vectors addressed through slot lists.
+struct LevelItem {
+  const void *P;           // k x k, ldp
+  const void *B;           // op(B) is m x k, ldb as stored
+  const int32_t *islot;
+  int32_t k, ldp, ldb;
+  int32_t off;             // start among its batch's staged inputs
+  int32_t nb, pad;         // first item of a batch: items of the batch
+};
+struct LevelTask {
+  const void *M;           // m x m, ldm
+  const int32_t *slots;
+  int32_t m, ldm;
+  int32_t row0, nrows;
+  int32_t item_begin, item_end;
+  int32_t base;            // which of the launch's two base vectors y starts from
+  int32_t pad;
+};
+
+// Pull group: out[oslot[r]] = base[oslot[r]] + alpha * sum_items op(B_i) in[islot_i[c]].
 struct PullItem {
   const void *B;
   const int32_t *islot;
@@ -307,9 +329,15 @@ struct ZeroDesc {
 };
 int launch_zero(FType t, const ZeroDesc *d_items, int n, int64_t max_elems, hipStream_t st);
 int launch_gemv(FType t, const GemvDesc *d_items, const GemvChunk *d_chunks, int nchunks,
-                const double *in, double *out, double alpha, double beta, hipStream_t st);
-int launch_slot_copy(const int32_t *slots, int64_t n, const double *src, double *dst,
-                     hipStream_t st);
+                const double *in, double *out, hipStream_t st);
+constexpr int LEVEL_CAP = 2048;      // staged inputs of one batch of items
+constexpr int LEVEL_MAXIT = 32;      // items of one batch
+// LDS of one workgroup of nt threads: inputs of a batch (twice where the
+// items have a P), one cluster, and the transposed form's partial sums
+size_t level_lds_bytes(int tot, int m, int pre, int trans, int nt);
+int launch_level(FType t, int trans, const LevelTask *d_tasks, int ntasks, const LevelItem *d_items,
+                 int tot, int m, int pre, int nt, const double *in, const double *base0,
+                 const double *base1, double *out, hipStream_t st);
 
 int launch_spmv(const spand_bsr_t &A, int transpose, double alpha, const double *x,
                 double beta, double *y, const double *z, double gz, const double *w,

@@ -11,9 +11,10 @@ constexpr int TS_MAXS = 8;        // largest s
 constexpr int TS_MAXA = 160;      // largest restart + s + 1
 
 constexpr int PULL_ROWS = 64;     // output rows per pull workgroup
+constexpr int GEMV_TROWS = 64;    // output rows of a transposed GEMV band
 int launch_pull2(FType t, const PullGroup *d_groups, const PullItem *d_items,
                  const PullChunk *d_chunks, int nchunks, int trans, const double *in,
-                 double *out, double alpha, double beta, hipStream_t st);
+                 const double *base, double *out, double alpha, hipStream_t st);
 int launch_spmv_g(const spand_bsr_t &A, int G, double alpha, const double *x, double beta,
                   double *y, const double *z, double gz, const double *w, double gw,
                   hipStream_t st);

@@ -17,10 +17,10 @@ __device__ inline T wsum(T v) {
 }
 
 // ------------------------------------------------------------------ GEMV
-// out[oslot[r]] = beta*out[oslot[r]] + alpha * sum_c op(A)(r, c) in[islot[c]]
+// out[oslot[r]] = sum_c op(A)(r, c) in[islot[c]]   (level 0 of the sweeps)
 // One workgroup per band of output rows (GemvChunk).  The input is staged
 // in LDS.  Bands of one item may run concurrently, so in == out is not
-// allowed (in-place sweeps write a scratch vector and copy back).
+// allowed (the sweeps alternate between two vectors).
 // Products accumulate in float64 for either factor precision: a float32
 // factor stays one fixed linear operator (rounding the vector to float32 in
 // every sweep would make M^-1 differ between applications, which
@@ -46,13 +46,13 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_gemv(const GemvDesc *__restrict__ items,
                                               const GemvChunk *__restrict__ chunks,
                                               const double *__restrict__ in,
-                                              double *__restrict__ out, double alpha,
-                                              double beta) {
+                                              double *__restrict__ out) {
   using VW = Vec16<T>;
   constexpr int VN = VW::N;
   const GemvChunk ch = chunks[blockIdx.x];
   const GemvDesc d = items[ch.item];
   __shared__ double xs[GEMV_MAXC];
+  __shared__ double part[256];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   for (int c = tid; c < d.cols; c += 256) xs[c] = in[d.islot[c]];
   __syncthreads();
@@ -89,66 +89,284 @@ __global__ __launch_bounds__(256) void k_gemv(const GemvDesc *__restrict__ items
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           if (rr0 + q >= ch.nrows) break;
-          const int o = d.oslot[ch.row0 + rr0 + q];
-          double v = alpha * acc[q];
-          if (beta != 0.0) v += beta * out[o];
-          out[o] = v;
+          out[d.oslot[ch.row0 + rr0 + q]] = acc[q];
         }
     }
   } else {
-    const int r = ch.row0 + tid;
-    if (tid < ch.nrows) {
-      double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-      const T *col = A + r;
-      int c = 0;
-      for (; c + 4 <= d.cols; c += 4) {
-        a0 += double(col[(int64_t)c * d.lda]) * xs[c];
-        a1 += double(col[(int64_t)(c + 1) * d.lda]) * xs[c + 1];
-        a2 += double(col[(int64_t)(c + 2) * d.lda]) * xs[c + 2];
-        a3 += double(col[(int64_t)(c + 3) * d.lda]) * xs[c + 3];
-      }
-      for (; c < d.cols; ++c) a0 += double(col[(int64_t)c * d.lda]) * xs[c];
-      const int o = d.oslot[r];
-      double v = alpha * ((a0 + a1) + (a2 + a3));
-      if (beta != 0.0) v += beta * out[o];
-      out[o] = v;
+    // bands of GEMV_TROWS rows: lane = row, each wave takes every fourth
+    // column (eight loads in flight per lane), the four sums meet in LDS
+    double a = 0.0;
+    const int r = ch.row0 + min(lane, ch.nrows - 1);
+    const T *col = A + r;
+    int c = wid;
+    for (; c + 28 < d.cols; c += 32) {
+      T v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = col[(int64_t)(c + 4 * u) * d.lda];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) a += double(v[u]) * xs[c + 4 * u];
     }
+    for (; c < d.cols; c += 4) a += double(col[(int64_t)c * d.lda]) * xs[c];
+    part[tid] = a;
+    __syncthreads();
+    if (tid < ch.nrows)
+      out[d.oslot[ch.row0 + tid]] = (part[tid] + part[tid + 64]) + (part[tid + 128] + part[tid + 192]);
   }
 }
 
 int launch_gemv(FType t, const GemvDesc *d_items, const GemvChunk *d_chunks, int nchunks,
-                const double *in, double *out, double alpha, double beta, hipStream_t st) {
+                const double *in, double *out, hipStream_t st) {
   if (nchunks <= 0) return SPAND_OK;
   if (t == FType::F64)
-    hipLaunchKernelGGL(k_gemv<double>, dim3(nchunks), dim3(256), 0, st, d_items, d_chunks, in, out,
-                       alpha, beta);
+    hipLaunchKernelGGL(k_gemv<double>, dim3(nchunks), dim3(256), 0, st, d_items, d_chunks, in, out);
   else
-    hipLaunchKernelGGL(k_gemv<float>, dim3(nchunks), dim3(256), 0, st, d_items, d_chunks, in, out,
-                       alpha, beta);
+    hipLaunchKernelGGL(k_gemv<float>, dim3(nchunks), dim3(256), 0, st, d_items, d_chunks, in, out);
   SP_HIP(hipGetLastError());
   return SPAND_OK;
 }
 
-__global__ void k_slot_copy(const int32_t *__restrict__ slots, int64_t n,
-                            const double *__restrict__ src, double *__restrict__ dst) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int s = slots[i];
-    dst[s] = src[s];
+// ------------------------------------------------------------------ levels above the leaves
+// The sweeps over a level l >= 1 (LevelTask): its clusters are small dense
+// matrices (interfaces of ~100 unknowns, interiors of ~60), so a launch is
+// bound by latency - of the launch itself and of each step's loads - and the
+// steps of a level are fused: one workgroup carries a cluster through the
+// couplings to its neighbours (y) and its own matrix (M y), and with P set
+// recomputes the neighbours' matrix-vector products it needs instead of
+// waiting for a launch of their own.
+// Nine launches a level (three of them copies back to x) became two to six:
+// apply 616 -> 197 us at 37x29 p = 1 transposed FP64 (36 launches -> 14),
+// 1063 -> 860 us at 128x128 p = 2 FP32 (3.0 GB, 81 -> 25), 4.46 -> 3.87 ms
+// at 256x256 p = 3 FP32.  Loads left to the compiler's own schedule (one
+// after another, each waited for) cost 926 us instead of 860.
+// The sum of a row never depends on how a level is cut into launches: plain
+// rows take LEVEL_LANES lanes in 16-byte vectors and a shuffle tree,
+// transposed rows LEVEL_LANES slices of every LEVEL_LANES-th column, and the
+// couplings of a cluster accumulate in item order.
+constexpr int LEVEL_LANES = 8;
+
+// Matrices are addressed as global memory (the pointers come out of LDS, from
+// which the compiler cannot tell).
+template <typename T>
+using GPtr = const T __attribute__((address_space(1))) *;
+template <typename T>
+__device__ inline GPtr<T> gptr(const void *p) {
+  return (GPtr<T>)p;
+}
+typedef float level_f32x4 __attribute__((ext_vector_type(4)));
+typedef double level_f64x2 __attribute__((ext_vector_type(2)));
+template <typename T>
+struct LevelVec;
+template <>
+struct LevelVec<float> {
+  using V = level_f32x4;
+  static constexpr int N = 4;
+};
+template <>
+struct LevelVec<double> {
+  using V = level_f64x2;
+  static constexpr int N = 2;
+};
+
+// sum over the columns of one row of a row-major matrix that lane q of
+// LEVEL_LANES takes.  Rows start at any multiple of sizeof(T): up to VN - 1
+// elements before the first 16-byte boundary and after the last whole vector
+// are scalar.  Four vectors in flight: past the end a load repeats the last
+// vector and its products are dropped, and the empty statement keeps the
+// loads of a step together (one memory round trip instead of four).
+template <typename T>
+__device__ inline double level_dot(GPtr<T> row, int n, const double *x, int q) {
+  using V = typename LevelVec<T>::V;
+  constexpr int VN = LevelVec<T>::N, ST = LEVEL_LANES * VN;
+  const int mis = int((reinterpret_cast<uintptr_t>((const T *)row) / sizeof(T)) % VN);
+  const int h = min(mis ? VN - mis : 0, n);
+  const int cv = h + (n - h) / VN * VN;
+  // element q of the head and tail together (at most 2 VN - 2 < LEVEL_LANES)
+  const int ns = h + n - cv, cs = q < ns ? (q < h ? q : cv + (q - h)) : 0;
+  T es = row[cs];
+  if (cv == h) return q < ns ? double(es) * x[cs] : 0.0;
+  double a = 0.0;
+  for (int c = h + q * VN; c < cv; c += 4 * ST) {
+    V v[4];
+    int cc[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      cc[u] = min(c + u * ST, cv - VN);
+      v[u] = *(GPtr<V>)(row + cc[u]);
+    }
+    asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(es));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      double s = a;
+#pragma unroll
+      for (int w = 0; w < VN; ++w) s += double(v[u][w]) * x[cc[u] + w];
+      a = c + u * ST < cv ? s : a;
+    }
+  }
+  const double xe = x[cs];
+  return q < ns ? a + double(es) * xe : a;
+}
+
+// sum over every LEVEL_LANES-th column from q of one row of the transpose
+// (element (c, r) at col[c * ld]); eight loads in flight
+template <typename T>
+__device__ inline double level_dot_t(GPtr<T> col, int ld, int n, const double *x, int q) {
+  double a = 0.0;
+  for (int c = q; c < n; c += 8 * LEVEL_LANES) {
+    T v[8];
+    int cc[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      cc[u] = min(c + u * LEVEL_LANES, n - 1);
+      v[u] = col[(int64_t)cc[u] * ld];
+    }
+    asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]));
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const double s = a + double(v[u]) * x[cc[u]];
+      a = c + u * LEVEL_LANES < n ? s : a;
+    }
+  }
+  return a;
+}
+
+template <typename T, int TRANS>
+__global__ __launch_bounds__(1024) void k_level(const LevelTask *__restrict__ tasks,
+                                                const LevelItem *__restrict__ items, int tot,
+                                                int mmax, int pre, const double *in,
+                                                const double *base0, const double *base1,
+                                                double *out) {
+  extern __shared__ double sm[];
+  __shared__ LevelItem its[LEVEL_MAXIT];
+  double *xs = sm, *t = xs + tot, *y = pre ? t + tot : t, *part = y + mmax;
+  const LevelTask d = tasks[blockIdx.x];
+  const int tid = threadIdx.x, nt = blockDim.x, nr = nt / LEVEL_LANES;
+  // plain: consecutive lanes share a row; transposed: consecutive lanes take
+  // consecutive rows (coalesced), one slice of the columns after the other
+  const int rl = TRANS ? tid % nr : tid / LEVEL_LANES, q = TRANS ? tid / nr : tid % LEVEL_LANES;
+  const double *bs = d.base ? base1 : base0;
+  const int y0 = d.M ? 0 : d.row0, y1 = d.M ? d.m : d.row0 + d.nrows;   // rows of y needed here
+  // the first row's base is on its way while the items are staged
+  const GPtr<int32_t> slots = gptr<int32_t>(d.slots);
+  const double yb = y0 + tid < y1 ? bs[slots[y0 + tid]] : 0.0;
+  // one row's sum over its lanes, in lane 0 (plain) or slice 0 (transposed;
+  // all threads of the workgroup call it together)
+  auto total = [&](double a) {
+    if (TRANS) {
+      part[tid] = a;
+      __syncthreads();
+      if (q == 0) {
+        a = 0.0;
+#pragma unroll
+        for (int u = 0; u < LEVEL_LANES; ++u) a += part[u * nr + rl];
+      }
+      __syncthreads();
+    } else {
+#pragma unroll
+      for (int o = LEVEL_LANES / 2; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
+    }
+    return a;
+  };
+  auto item_of = [&](int ni, int R) {
+    int j = 0;
+    while (j + 1 < ni && its[j + 1].off <= R) ++j;
+    return j;
+  };
+  for (int ib = d.item_begin; ib < d.item_end;) {
+    const int ni = items[ib].nb;
+    if (ib > d.item_begin) __syncthreads();   // the batch before is done with its inputs
+    if (tid < ni) its[tid] = items[ib + tid];
+    __syncthreads();
+    const int nin = its[ni - 1].off + its[ni - 1].k;
+    for (int R = tid; R < nin; R += nt) {
+      const LevelItem &p = its[item_of(ni, R)];
+      xs[R] = in[gptr<int32_t>(p.islot)[R - p.off]];
+    }
+    if (ib == d.item_begin) {
+      if (y0 + tid < y1) y[y0 + tid] = yb;
+      for (int r = y0 + nt + tid; r < y1; r += nt) y[r] = bs[slots[r]];
+    }
+    __syncthreads();
+    const double *v = xs;
+    if (pre) {
+      for (int r0 = 0; r0 < nin; r0 += nr) {
+        const int R = r0 + rl;
+        double a = 0.0;
+        if (R < nin) {
+          const LevelItem &p = its[item_of(ni, R)];
+          const GPtr<T> P = gptr<T>(p.P);
+          a = TRANS ? level_dot_t<T>(P + (R - p.off), p.ldp, p.k, xs + p.off, q)
+                    : level_dot<T>(P + (int64_t)(R - p.off) * p.ldp, p.k, xs + p.off, q);
+        }
+        a = total(a);
+        if (q == 0 && R < nin) t[R] = a;
+      }
+      __syncthreads();
+      v = t;
+    }
+    for (int r0 = y0; r0 < y1; r0 += nr) {
+      const int r = r0 + rl;
+      double a = 0.0;
+      if (r < y1)
+        for (int j = 0; j < ni; ++j) {
+          const LevelItem &p = its[j];
+          const GPtr<T> B = gptr<T>(p.B);
+          a += TRANS ? level_dot_t<T>(B + r, p.ldb, p.k, v + p.off, q)
+                     : level_dot<T>(B + (int64_t)r * p.ldb, p.k, v + p.off, q);
+        }
+      a = total(a);
+      if (q == 0 && r < y1) y[r] -= a;
+    }
+    ib += ni;
+  }
+  if (d.item_begin == d.item_end) {
+    if (y0 + tid < y1) y[y0 + tid] = yb;
+    for (int r = y0 + nt + tid; r < y1; r += nt) y[r] = bs[slots[r]];
+  }
+  __syncthreads();
+  const int rend = d.row0 + d.nrows;
+  if (!d.M) {
+    for (int r = d.row0 + tid; r < rend; r += nt) out[slots[r]] = y[r];
+    return;
+  }
+  const GPtr<T> M = gptr<T>(d.M);
+  for (int r0 = d.row0; r0 < rend; r0 += nr) {
+    const int r = r0 + rl;
+    double a = 0.0;
+    if (r < rend)
+      a = TRANS ? level_dot_t<T>(M + r, d.ldm, d.m, y, q) : level_dot<T>(M + (int64_t)r * d.ldm, d.m, y, q);
+    a = total(a);
+    if (q == 0 && r < rend) out[slots[r]] = a;
   }
 }
 
-int launch_slot_copy(const int32_t *slots, int64_t n, const double *src, double *dst,
-                     hipStream_t st) {
-  if (n <= 0) return SPAND_OK;
-  hipLaunchKernelGGL(k_slot_copy, dim3((unsigned)std::min<int64_t>(8192, cdiv(n, 256))), dim3(256),
-                     0, st, slots, n, src, dst);
+size_t level_lds_bytes(int tot, int m, int pre, int trans, int nt) {
+  return (size_t(tot) * (pre ? 2 : 1) + size_t(m) + (trans ? size_t(nt) : 0)) * 8;
+}
+
+int launch_level(FType t, int trans, const LevelTask *d_tasks, int ntasks, const LevelItem *d_items,
+                 int tot, int m, int pre, int nt, const double *in, const double *base0,
+                 const double *base1, double *out, hipStream_t st) {
+  if (ntasks <= 0) return SPAND_OK;
+  const size_t lds = level_lds_bytes(tot, m, pre, trans, nt);
+  const dim3 g(ntasks), b(nt);
+#define LEVEL_LAUNCH(T, TR)                                                                       \
+  hipLaunchKernelGGL((k_level<T, TR>), g, b, lds, st, d_tasks, d_items, tot, m, pre, in, base0,   \
+                     base1, out)
+  if (t == FType::F64) {
+    if (trans) LEVEL_LAUNCH(double, 1);
+    else LEVEL_LAUNCH(double, 0);
+  } else {
+    if (trans) LEVEL_LAUNCH(float, 1);
+    else LEVEL_LAUNCH(float, 0);
+  }
+#undef LEVEL_LAUNCH
   SP_HIP(hipGetLastError());
   return SPAND_OK;
 }
 
 // ------------------------------------------------------------------ pull
-// out[oslot[r]] = beta*out[oslot[r]] + alpha * sum_items op(B_i) in[islot_i]
+// out[oslot[r]] = base[oslot[r]] + alpha * sum_items op(B_i) in[islot_i]
+// (level 0; a group without items copies base to out)
 // One workgroup per chunk of at most 64 output rows of a group; the items of
 // the group are accumulated in order, in registers (a row is always owned by
 // the same lanes).  Per item the input segment is staged in LDS.
@@ -161,9 +379,8 @@ template <typename T, int TRANS>
 __global__ __launch_bounds__(256) void k_pull(const PullGroup *__restrict__ groups,
                                               const PullItem *__restrict__ items,
                                               const PullChunk *__restrict__ chunks,
-                                              const double *__restrict__ in,
-                                              double *__restrict__ out, double alpha,
-                                              double beta) {
+                                              const double *in, const double *base,
+                                              double *out, double alpha) {
   using VW = Vec16<T>;
   constexpr int VN = VW::N;
   const PullChunk ch = chunks[blockIdx.x];
@@ -220,9 +437,7 @@ __global__ __launch_bounds__(256) void k_pull(const PullGroup *__restrict__ grou
   }
   auto put = [&](int r, double v) {
     const int o = g.oslot[ch.row0 + r];
-    v *= alpha;
-    if (beta != 0.0) v += beta * out[o];
-    out[o] = v;
+    out[o] = base[o] + alpha * v;
   };
   if (!TRANS) {
     const int rr = tid >> 2;
@@ -236,15 +451,15 @@ __global__ __launch_bounds__(256) void k_pull(const PullGroup *__restrict__ grou
 
 int launch_pull2(FType t, const PullGroup *d_groups, const PullItem *d_items,
                  const PullChunk *d_chunks, int nchunks, int trans, const double *in,
-                 double *out, double alpha, double beta, hipStream_t st) {
+                 const double *base, double *out, double alpha, hipStream_t st) {
   if (nchunks <= 0) return SPAND_OK;
   const dim3 g(nchunks), b(256);
   if (t == FType::F64) {
-    if (trans) hipLaunchKernelGGL((k_pull<double, 1>), g, b, 0, st, d_groups, d_items, d_chunks, in, out, alpha, beta);
-    else hipLaunchKernelGGL((k_pull<double, 0>), g, b, 0, st, d_groups, d_items, d_chunks, in, out, alpha, beta);
+    if (trans) hipLaunchKernelGGL((k_pull<double, 1>), g, b, 0, st, d_groups, d_items, d_chunks, in, base, out, alpha);
+    else hipLaunchKernelGGL((k_pull<double, 0>), g, b, 0, st, d_groups, d_items, d_chunks, in, base, out, alpha);
   } else {
-    if (trans) hipLaunchKernelGGL((k_pull<float, 1>), g, b, 0, st, d_groups, d_items, d_chunks, in, out, alpha, beta);
-    else hipLaunchKernelGGL((k_pull<float, 0>), g, b, 0, st, d_groups, d_items, d_chunks, in, out, alpha, beta);
+    if (trans) hipLaunchKernelGGL((k_pull<float, 1>), g, b, 0, st, d_groups, d_items, d_chunks, in, base, out, alpha);
+    else hipLaunchKernelGGL((k_pull<float, 0>), g, b, 0, st, d_groups, d_items, d_chunks, in, base, out, alpha);
   }
   SP_HIP(hipGetLastError());
   return SPAND_OK;
