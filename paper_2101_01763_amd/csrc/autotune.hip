@@ -135,7 +135,7 @@ int autotune_gemv(FType t, int bs, const std::function<int(int, GemvSet &)> &bui
     GemvSet g;
     SP_TRY(build(R, g));
     const float tm = time_median(st, [&]() {
-      return launch_gemv(t, g.d_items, g.d_chunks, g.nchunks, in, out, st);
+      return launch_gemv(t, g.d_items, g.d_chunks, g.nchunks, in, nullptr, nullptr, out, st);
     });
     if (tm < bt) {
       bt = tm;

@@ -44,7 +44,9 @@ struct GemvSet {
   GemvChunk *d_chunks = nullptr;
   int nchunks = 0;
   int n = 0;
-  int set(Factor &F, std::vector<GemvDesc> items, int trans, int rows = 0);
+  // rows of an item: GEMV_PLAIN all, GEMV_EDGE the nb first (as plain
+  // products), GEMV_INNER all, as the edge and inner bands
+  int set(Factor &F, std::vector<GemvDesc> items, int trans, int rows = 0, int part = GEMV_PLAIN);
 };
 
 // one launch of k_level: clusters of a level >= 1
@@ -69,12 +71,13 @@ struct LevelSweep {
 // apply plan of one level (see Factor::sweeps)
 struct ApplyLevel {
   // level 0
-  GemvSet inv, invT;            // interiors: A_ss^-1
+  GemvSet inv, invT;            // interiors: A_ss^-1, the rows next to separators (forward)
+  GemvSet invb, invbT;          // and in two parts (backward, see k_gemv)
   GemvSet F, B, FT, BT;         // interfaces
   PullSet fw;    // x_n -= A_ns t_s          (groups: neighbours)
-  PullSet bw;    // x_s -= A_sn x_n          (groups: interiors)
+  PullSet bw;    // c_s = -A_sn x_n          (groups: interiors)
   PullSet tfw;   // x_n -= A_sn^T t_s        (groups: neighbours)
-  PullSet tbw;   // x_s -= A_ns^T x_n        (groups: interiors)
+  PullSet tbw;   // c_s = -A_ns^T x_n        (groups: interiors)
   // levels >= 1: forward and backward sweep, plain and transposed
   LevelSweep fwd[2], bwd[2];
 };
@@ -185,7 +188,7 @@ struct Factor {
   Bump retired;                 // scratch of finished levels, released at the next sync
   size_t keep_bytes = 0;
   int32_t *d_iota = nullptr;
-  double *d_tbuf = nullptr;
+  double *d_tbuf = nullptr, *d_cbuf = nullptr;   // scratch vectors of the sweeps
   int *d_flag = nullptr;
   // statistics
   std::vector<RankStat> ranks;
@@ -220,9 +223,10 @@ struct Factor {
   int gemv_rows = 64;              // band height of the sweep GEMVs (autotuned)
   bool use_graphs = true;          // replay the sweeps from captured hipGraphs
   hipGraphExec_t gexec[2] = {nullptr, nullptr};
-  double *d_xg = nullptr;          // the graphs' fixed input/output vector
+  double *d_xg = nullptr, *d_xr = nullptr;   // the graphs' fixed input and result vectors
   ~Factor();
-  int sweeps(const std::vector<ApplyLevel> &plan, double *x, int transpose, hipStream_t st);
+  int sweeps(const std::vector<ApplyLevel> &plan, const double *x, double *out, int transpose,
+             hipStream_t st);
   int capture(int member, int transpose);
   int capture_graphs(int which = 3, int member = -1);
   // the sweep sets of every system from the sets of all unknowns (gs: the
@@ -230,7 +234,7 @@ struct Factor {
   int member_pull(int l, PullSet ApplyLevel::*which, const std::vector<PullGroup> &G,
                   const std::vector<PullItem> &I, const std::vector<int> &gs);
   int member_gemv(int l, GemvSet ApplyLevel::*which, const std::vector<GemvDesc> &gv,
-                  const std::vector<int> &gs, int trans);
+                  const std::vector<int> &gs, int trans, int part = GEMV_PLAIN);
   int level_sets(int l, const LevelSource &src);
   int level_plan(ApplyLevel &AL, const LevelSource &src);
   int dalloc(void **p, size_t bytes, bool keep);

@@ -161,12 +161,12 @@ int Factor::member_pull(int l, PullSet ApplyLevel::*which, const std::vector<Pul
 }
 
 int Factor::member_gemv(int l, GemvSet ApplyLevel::*which, const std::vector<GemvDesc> &gv,
-                        const std::vector<int> &gs, int trans) {
+                        const std::vector<int> &gs, int trans, int part) {
   if (members.empty()) return SPAND_OK;
   std::vector<std::vector<GemvDesc>> gm(members.size());
   for (size_t i = 0; i < gv.size(); ++i) gm[size_t(gs[i])].push_back(gv[i]);
   for (size_t m = 0; m < members.size(); ++m)
-    SP_TRY((members[m].lv[size_t(l)].*which).set(*this, gm[m], trans));
+    SP_TRY((members[m].lv[size_t(l)].*which).set(*this, gm[m], trans, 0, part));
   return SPAND_OK;
 }
 
@@ -768,6 +768,28 @@ int Factor::level0(const NDResult &nd, LevelState &S) {
       ecl[cl[c].elems[q]] = c;
       epos[cl[c].elems[q]] = int(q);
     }
+  // In the stored inverse of a leaf (and in its slot list) the elements next
+  // to a separator come first: the sweeps need only their rows and columns of
+  // parts of it.  The elimination itself keeps the elements' own order.
+  std::vector<std::vector<int>> lel(ncl);   // a leaf's elements as stored
+  std::vector<int> nedge(ncl, 0), spos(epos);
+  std::vector<int32_t> sto;                 // place of every element, leaf after leaf
+  std::vector<size_t> sto0(ncl, 0);
+  for (int c = 0; c < ncl; ++c) {
+    if (!cl[c].interior) continue;
+    std::vector<int> inner;
+    for (int e : cl[c].elems) {
+      bool edge = false;
+      for (int t = h_rowptr[e]; t < h_rowptr[e + 1] && !edge; ++t)
+        edge = !cl[ecl[h_colind[t]]].interior;
+      (edge ? lel[c] : inner).push_back(e);
+    }
+    nedge[c] = int(lel[c].size());
+    lel[c].insert(lel[c].end(), inner.begin(), inner.end());
+    for (size_t q = 0; q < lel[c].size(); ++q) spos[lel[c][q]] = int(q);
+    sto0[c] = sto.size();
+    for (int e : cl[c].elems) sto.push_back(spos[e]);
+  }
   S.size.assign(ncl, 0);
   S.interior.assign(ncl, 0);
   for (int c = 0; c < ncl; ++c) {
@@ -840,9 +862,12 @@ int Factor::level0(const NDResult &nd, LevelState &S) {
     SP_TRY(elim_batch(items, 0));
     trace("elim enqueue", 0);
     std::vector<RowGatherDesc> rg;
+    int32_t *d_sto;
+    SP_TRY(upload(sto, &d_sto, false));
     for (auto &d : items) {
-      // find the leaf whose A_ss this is
       RowGatherDesc g{};
+      g.sto = d_sto + sto0[d.pad];
+      g.b = b;
       g.src = d.A;
       g.piv = d.piv;
       g.n = d.n;
@@ -866,7 +891,7 @@ int Factor::level0(const NDResult &nd, LevelState &S) {
     auto &sl = S.slots[c];
     sl.resize(size_t(S.size[c]));
     size_t o = 0;
-    for (int e : cl[c].elems)
+    for (int e : cl[c].interior ? lel[c] : cl[c].elems)
       for (int q = 0; q < b; ++q) sl[o++] = e * b + q;
   }
   SP_TRY(upload_level_slots(S));
@@ -1063,7 +1088,7 @@ int Factor::level0(const NDResult &nd, LevelState &S) {
             SchurItem it{};
             it.A1 = cpl_ns(s, ia);     // A[e_a, f_a]
             it.A2 = cpl_sn(s, ic);     // A[f_c, e_c]
-            it.Y = (char *)Ainv[s] + (size_t(epos[ca.f]) * b * ld4(n) + size_t(epos[cc.f]) * b) * tsz;
+            it.Y = (char *)Ainv[s] + (size_t(spos[ca.f]) * b * ld4(n) + size_t(spos[cc.f]) * b) * tsz;
             it.ldy = ld4(n);
             SchurGroup &g = groups[item_tid[q++]];
             items[g.item_end++] = it;
@@ -1116,16 +1141,10 @@ int Factor::level0(const NDResult &nd, LevelState &S) {
     // one pull group per key element; half = 0 takes A[e, f], 1 A[f, e]
     auto build = [&](const std::vector<int> &off, const std::vector<std::pair<int, size_t>> &lst,
                      int half, int trans, std::vector<PullGroup> &G, std::vector<PullItem> &I,
-                     std::vector<int> &gs, bool all_leaf) {
+                     std::vector<int> &gs, bool all_sep) {
       std::vector<int> keys;
-      if (all_leaf) {
-        for (int s : leaves)
-          for (int f : cl[s].elems) keys.push_back(f);
-        std::sort(keys.begin(), keys.end());
-      } else {
-        for (int e = 0; e < K; ++e)
-          if (off[size_t(e) + 1] > off[size_t(e)]) keys.push_back(e);
-      }
+      for (int e = 0; e < K; ++e)
+        if (off[size_t(e) + 1] > off[size_t(e)] || (all_sep && !S.interior[ecl[e]])) keys.push_back(e);
       G.reserve(keys.size());
       I.reserve(lst.size());
       gs.reserve(keys.size());
@@ -1150,20 +1169,20 @@ int Factor::level0(const NDResult &nd, LevelState &S) {
     };
     // each set is uploaded at the next rank read-back
     auto emit = [&](const std::vector<int> &off, const std::vector<std::pair<int, size_t>> &lst,
-                    int half, int trans, bool all_leaf, PullSet ApplyLevel::*which) {
+                    int half, int trans, bool all_sep, PullSet ApplyLevel::*which) {
       std::vector<PullGroup> G;
       std::vector<PullItem> I;
       std::vector<int> gs;
-      build(off, lst, half, trans, G, I, gs, all_leaf);
+      build(off, lst, half, trans, G, I, gs, all_sep);
       defer([this, &AL, which, G = std::move(G), I = std::move(I), gs = std::move(gs)]() {
         SP_TRY((AL.*which).set(*this, G, I));
         return member_pull(0, which, G, I, gs);
       });
     };
-    emit(off_e, by_e, 0, 0, false, &ApplyLevel::fw);    // x_n -= A_ns t_s
-    emit(off_f, by_f, 1, 0, true, &ApplyLevel::bw);     // x_s -= A_sn x_n
-    emit(off_e, by_e, 1, 1, false, &ApplyLevel::tfw);   // x_n -= A_sn^T t_s
-    emit(off_f, by_f, 0, 1, true, &ApplyLevel::tbw);    // x_s -= A_ns^T x_n
+    emit(off_e, by_e, 0, 0, true, &ApplyLevel::fw);     // x_n -= A_ns t_s
+    emit(off_f, by_f, 1, 0, false, &ApplyLevel::bw);    // c_s = -A_sn x_n
+    emit(off_e, by_e, 1, 1, true, &ApplyLevel::tfw);    // x_n -= A_sn^T t_s
+    emit(off_f, by_f, 0, 1, false, &ApplyLevel::tbw);   // c_s = -A_ns^T x_n
     trace("pull sets", 0);
     std::vector<GemvDesc> gv;
     std::vector<int> vs;
@@ -1173,9 +1192,11 @@ int Factor::level0(const NDResult &nd, LevelState &S) {
       d.islot = d.oslot = S.d_slots[s];
       d.rows = d.cols = S.size[s];
       d.lda = ld4(S.size[s]);
+      d.nb = nedge[s] * b;
       gv.push_back(d);
       vs.push_back(csys(0, s));
-      acct(csys(0, s), double(S.size[s]) * S.size[s] * tsz * 2, 0.0);   // A_ss^-1: both sweeps
+      // A_ss^-1: the parts the two sweeps read
+      acct(csys(0, s), (double(S.size[s]) * S.size[s] + double(d.nb) * d.nb) * tsz, 0.0);
     }
     // band height of the sweep GEMVs: autotuned once per (precision, b)
     defer([this, &AL, gv, vs]() -> int {
@@ -1184,10 +1205,14 @@ int Factor::level0(const NDResult &nd, LevelState &S) {
       SP_HIP(hipMemsetAsync(tin, 0, size_t(N) * 8, stream));
       auto build_set = [&](int R, GemvSet &g) { return g.set(*this, gv, 0, R); };
       SP_TRY(autotune_gemv(ft, bs, build_set, (double *)tin, d_tbuf, stream, &gemv_rows));
-      SP_TRY(AL.inv.set(*this, gv, 0));
-      SP_TRY(AL.invT.set(*this, gv, 1));
-      SP_TRY(member_gemv(0, &ApplyLevel::inv, gv, vs, 0));
-      return member_gemv(0, &ApplyLevel::invT, gv, vs, 1);
+      SP_TRY(AL.inv.set(*this, gv, 0, 0, GEMV_EDGE));
+      SP_TRY(AL.invT.set(*this, gv, 1, 0, GEMV_EDGE));
+      SP_TRY(AL.invb.set(*this, gv, 0, 0, GEMV_INNER));
+      SP_TRY(AL.invbT.set(*this, gv, 1, 0, GEMV_INNER));
+      SP_TRY(member_gemv(0, &ApplyLevel::inv, gv, vs, 0, GEMV_EDGE));
+      SP_TRY(member_gemv(0, &ApplyLevel::invT, gv, vs, 1, GEMV_EDGE));
+      SP_TRY(member_gemv(0, &ApplyLevel::invb, gv, vs, 0, GEMV_INNER));
+      return member_gemv(0, &ApplyLevel::invbT, gv, vs, 1, GEMV_INNER);
     });
     trace("inverse sweep sets", 0);
     for (int s : leaves)   // A_ns forward, A_sn backward; the inversion
@@ -1241,7 +1266,7 @@ int PullSet::set(Factor &F, std::vector<PullGroup> G, const std::vector<PullItem
   return SPAND_OK;
 }
 
-int GemvSet::set(Factor &F, std::vector<GemvDesc> items, int trans, int rows) {
+int GemvSet::set(Factor &F, std::vector<GemvDesc> items, int trans, int rows, int part) {
   n = int(items.size());
   if (!n) return SPAND_OK;
   int R = trans ? GEMV_TROWS : (rows > 0 ? rows : F.gemv_rows);
@@ -1251,14 +1276,22 @@ int GemvSet::set(Factor &F, std::vector<GemvDesc> items, int trans, int rows) {
     // bound by the passes' latency, not by bytes.  Each row's sum is the
     // same whatever the band.
     int64_t tot = 0;
-    for (const auto &d : items) tot += d.rows;
+    for (const auto &d : items) tot += part == GEMV_EDGE ? d.nb : d.rows;
     while (R > 16 && tot < int64_t(R) * 4096) R /= 2;
   }
   std::vector<GemvChunk> ch;
   for (int i = 0; i < n; ++i) {
-    items[i].trans = trans;
-    for (int r0 = 0; r0 < items[i].rows; r0 += R)
-      ch.push_back(GemvChunk{i, r0, std::min(R, items[i].rows - r0), 0});
+    GemvDesc &d = items[i];
+    d.trans = trans;
+    auto bands = [&](int a, int b, int kind) {
+      for (int r0 = a; r0 < b; r0 += R) ch.push_back(GemvChunk{i, r0, std::min(R, b - r0), kind});
+    };
+    if (part == GEMV_INNER) {
+      bands(0, d.nb, GEMV_EDGE);
+      bands(d.nb, d.rows, GEMV_INNER);
+    } else {
+      bands(0, part == GEMV_EDGE ? d.nb : d.rows, GEMV_PLAIN);
+    }
   }
   nchunks = int(ch.size());
   SP_TRY(F.upload_parts({Factor::part(items, &d_items), Factor::part(ch, &d_chunks)}, true));
@@ -1303,7 +1336,7 @@ void LevelSet::add(const void *M, int ldm, const int32_t *slots, int size, int r
 }
 
 // The sweeps over one level: V is the vector that holds the level's unknowns
-// (x at even levels, the scratch vector at odd ones), O the other one.
+// (d_tbuf at odd levels, d_cbuf at even ones), O the other one.
 //   forward   t_s = A_ss^-1 x_s        (V -> O)
 //             y_n = x_n - sum A_ns t_s
 //             O_n = F_n y_n
@@ -2350,6 +2383,10 @@ int Factor::numeric() {
   d_tbuf = (double *)p;
   SP_TRY(dalloc(&p, size_t(N) * 8, true));
   d_xg = (double *)p;
+  SP_TRY(dalloc(&p, size_t(N) * 8, true));
+  d_xr = (double *)p;
+  SP_TRY(dalloc(&p, size_t(N) * 8, true));
+  d_cbuf = (double *)p;
   use_graphs = (opts.flags & SPAND_FLAG_NO_GRAPH) == 0 && !std::getenv("SPAND_NO_GRAPH");
   {
     const int tr = tuned_gemv_rows(ft, bs);
@@ -2411,32 +2448,37 @@ int Factor::numeric() {
 // y = M^-1 r:  forward over levels applies L' (interiors: x_n -= A_ns A_ss^-1 x_s)
 // and F_s (interfaces); backward applies B_s and R' (x_s = A_ss^-1 (x_s - A_sn x_n)).
 // y = M^-T r:  forward applies R'^T and B_s^T, backward F_s^T and L'^T.
-// A level's unknowns live in x (even levels) or d_tbuf (odd levels): every
-// step reads one vector and writes the other, so that nothing is copied back
-// and the backward sweep finds the interiors' forward values untouched.
-int Factor::sweeps(const std::vector<ApplyLevel> &lv, double *x, int transpose, hipStream_t st) {
+// x is only read, out only written (they must differ).  The leaves' forward
+// rows t stay in d_tbuf until the backward sweep.  A level's unknowns (l >= 1)
+// live in d_tbuf (odd levels) or d_cbuf (even ones): every step reads one
+// vector and writes the other, so that nothing is copied back and the
+// backward sweep finds the interiors' forward values untouched.
+// Level 0 with the parts of the leaf inverses that are needed, against both
+// whole (n^2 + nb^2 of 2 n^2 elements): apply 1342 -> 1176 us at 128x128
+// p = 2 FP64 (leaves of 7 x 3 elements, 16 of 21 at the edge), 543 -> 441 us
+// at 160x120 p = 1 FP32 (7 x 7, 24 of 49), 3.87 -> 3.74 ms at 256x256 p = 3
+// FP32 (3 x 3, 8 of 9).
+int Factor::sweeps(const std::vector<ApplyLevel> &lv, const double *x, double *out, int transpose,
+                   hipStream_t st) {
   const int L = int(lv.size());
-  double *V[2] = {x, d_tbuf};
-  auto gemv = [&](const GemvSet &g, const double *in, double *out) {
-    return g.n ? launch_gemv(ft, g.d_items, g.d_chunks, g.nchunks, in, out, st) : SPAND_OK;
+  double *V[2] = {d_cbuf, d_tbuf};
+  auto gemv = [&](const GemvSet &g, const double *in, double *to) {
+    return g.n ? launch_gemv(ft, g.d_items, g.d_chunks, g.nchunks, in, d_cbuf, d_tbuf, to, st) : SPAND_OK;
   };
-  auto pull = [&](const PullSet &p, const double *in, const double *base, double *out) {
+  auto pull = [&](const PullSet &p, const double *in, const double *base, double *to) {
     return p.n ? launch_pull2(ft, p.d_groups, p.d_items, p.d_chunks, p.nchunks, p.trans, in, base,
-                              out, -1.0, st)
+                              to, -1.0, st)
                : SPAND_OK;
   };
-  auto level = [&](const LevelSet &s, const double *in, const double *b0, const double *b1, double *out) {
+  auto level = [&](const LevelSet &s, const double *in, const double *b0, const double *b1, double *to) {
     return launch_level(ft, transpose, s.d_tasks, s.n, s.d_items, s.tot, s.m, s.pre, s.nt, in, b0,
-                        b1, out, st);
+                        b1, to, st);
   };
   if (L > 0) {
     const ApplyLevel &A = lv[0];
-    const PullSet &fw = transpose ? A.tfw : A.fw;
-    if (fw.n) {
-      SP_TRY(gemv(transpose ? A.invT : A.inv, V[0], V[1]));
-      SP_TRY(pull(fw, V[1], V[0], V[0]));
-    }
-    SP_TRY(gemv(transpose ? A.BT : A.F, V[0], V[1]));
+    SP_TRY(gemv(transpose ? A.invT : A.inv, x, d_tbuf));
+    SP_TRY(pull(transpose ? A.tfw : A.fw, d_tbuf, x, d_cbuf));
+    SP_TRY(gemv(transpose ? A.BT : A.F, d_cbuf, d_tbuf));
   }
   for (int l = 1; l < L; ++l) {
     const LevelSweep &w = lv[l].fwd[transpose];
@@ -2454,15 +2496,15 @@ int Factor::sweeps(const std::vector<ApplyLevel> &lv, double *x, int transpose, 
   }
   if (L > 0) {
     const ApplyLevel &A = lv[0];
-    SP_TRY(gemv(transpose ? A.FT : A.B, V[1], V[0]));
-    SP_TRY(pull(transpose ? A.tbw : A.bw, V[0], V[0], V[1]));
-    SP_TRY(gemv(transpose ? A.invT : A.inv, V[1], V[0]));
+    SP_TRY(gemv(transpose ? A.FT : A.B, d_tbuf, out));
+    SP_TRY(pull(transpose ? A.tbw : A.bw, out, nullptr, d_cbuf));
+    SP_TRY(gemv(transpose ? A.invbT : A.invb, x, out));
   }
   return SPAND_OK;
 }
 
-// Capture the sweeps on the fixed vector d_xg once; replays need one launch.
-// member >= 0: the sweeps of that system of a batch (its share of d_xg).
+// Capture the sweeps from d_xg to d_xr once; replays need one launch.
+// member >= 0: the sweeps of that system of a batch (its share of the vectors).
 int Factor::capture(int member, int transpose) {
   const std::vector<ApplyLevel> &plan = member < 0 ? lv : members[size_t(member)].lv;
   hipGraphExec_t *ge = member < 0 ? gexec : members[size_t(member)].gexec;
@@ -2475,7 +2517,7 @@ int Factor::capture(int member, int transpose) {
     r = SPAND_EHIP;
   }
   if (r == SPAND_OK) {
-    const int rs = sweeps(plan, d_xg, transpose, cs);
+    const int rs = sweeps(plan, d_xg, d_xr, transpose, cs);
     const hipError_t e = hipStreamEndCapture(cs, &g);
     if (rs != SPAND_OK) r = rs;
     else if (e != hipSuccess || !g) {
@@ -2512,23 +2554,23 @@ int Factor::capture_graphs(int which, int member) {
 
 int Factor::apply(const double *in, double *out, int transpose, hipStream_t st, int member) {
   if (member >= 0) {
-    // one system of a batch: its vector goes through its share of d_xg (the
-    // sweeps address the unknowns of the whole batch)
+    // one system of a batch: its vector goes through its share of d_xg and
+    // d_xr (the sweeps address the unknowns of the whole batch)
     const Member &M = members[size_t(member)];
-    double *seg = d_xg + M.dof_off;
-    SP_HIP(hipMemcpyAsync(seg, in, size_t(M.N) * 8, hipMemcpyDeviceToDevice, st));
+    SP_HIP(hipMemcpyAsync(d_xg + M.dof_off, in, size_t(M.N) * 8, hipMemcpyDeviceToDevice, st));
     if (use_graphs && M.gexec[transpose]) SP_HIP(hipGraphLaunch(M.gexec[transpose], st));
-    else SP_TRY(sweeps(M.lv, d_xg, transpose, st));
-    SP_HIP(hipMemcpyAsync(out, seg, size_t(M.N) * 8, hipMemcpyDeviceToDevice, st));
+    else SP_TRY(sweeps(M.lv, d_xg, d_xr, transpose, st));
+    SP_HIP(hipMemcpyAsync(out, d_xr + M.dof_off, size_t(M.N) * 8, hipMemcpyDeviceToDevice, st));
     return SPAND_OK;
   }
-  if (!use_graphs || !gexec[transpose]) {
-    if (out != in) SP_HIP(hipMemcpyAsync(out, in, size_t(N) * 8, hipMemcpyDeviceToDevice, st));
-    return sweeps(lv, out, transpose, st);
+  const bool graph = use_graphs && gexec[transpose];
+  if (graph || in == out) {
+    SP_HIP(hipMemcpyAsync(d_xg, in, size_t(N) * 8, hipMemcpyDeviceToDevice, st));
+    in = d_xg;
   }
-  SP_HIP(hipMemcpyAsync(d_xg, in, size_t(N) * 8, hipMemcpyDeviceToDevice, st));
+  if (!graph) return sweeps(lv, in, out, transpose, st);
   SP_HIP(hipGraphLaunch(gexec[transpose], st));
-  SP_HIP(hipMemcpyAsync(out, d_xg, size_t(N) * 8, hipMemcpyDeviceToDevice, st));
+  SP_HIP(hipMemcpyAsync(out, d_xr, size_t(N) * 8, hipMemcpyDeviceToDevice, st));
   return SPAND_OK;
 }
 
@@ -2538,9 +2580,9 @@ int Factor::apply_batch(const std::vector<const double *> &in, const std::vector
     SP_HIP(hipMemcpyAsync(d_xg + members[m].dof_off, in[m], size_t(members[m].N) * 8,
                           hipMemcpyDeviceToDevice, st));
   if (use_graphs && gexec[transpose]) SP_HIP(hipGraphLaunch(gexec[transpose], st));
-  else SP_TRY(sweeps(lv, d_xg, transpose, st));
+  else SP_TRY(sweeps(lv, d_xg, d_xr, transpose, st));
   for (size_t m = 0; m < members.size(); ++m)
-    SP_HIP(hipMemcpyAsync(out[m], d_xg + members[m].dof_off, size_t(members[m].N) * 8,
+    SP_HIP(hipMemcpyAsync(out[m], d_xr + members[m].dof_off, size_t(members[m].N) * 8,
                           hipMemcpyDeviceToDevice, st));
   return SPAND_OK;
 }

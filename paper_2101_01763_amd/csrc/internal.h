@@ -88,6 +88,18 @@ enum class FType { F64 = 0, F32 = 1 };
 inline size_t fsize(FType t) { return t == FType::F64 ? 8 : 4; }
 
 // ----------------------------------------------------------------- kernel descriptors
+#if defined(__HIPCC__)
+// A descriptor's pointer as a pointer to global memory.  Loaded from a
+// struct it is generic to the compiler, whose flat loads count against the
+// LDS counter too: every wait for an LDS read then also waits for all matrix
+// loads in flight.
+template <typename T>
+__device__ inline T *gmem(const void *p) {
+  // by way of an integer: a plain cast to the address space and back folds away
+  return (T *)(T __attribute__((address_space(1))) *)(uintptr_t)p;
+}
+#endif
+
 // All descriptors hold byte offsets / element pointers into device memory;
 // they are built and bounds-checked on the host, then uploaded.
 
@@ -154,10 +166,15 @@ struct GemvDesc {
   int32_t rows, cols;      // of op(A)
   int32_t lda;             // of A as stored (a multiple of 4)
   int32_t trans;
+  int32_t nb, pad;         // leaves: unknowns that touch a separator (they come first)
 };
 // a band of output rows of one GEMV item (one workgroup)
+//   GEMV_PLAIN   out = op(A) in
+//   GEMV_EDGE    out = add + op(A)[:, 0:nb] corr       (rows below nb)
+//   GEMV_INNER   out = op(A) (in + corr on 0:nb)       (rows from nb on)
+constexpr int GEMV_PLAIN = 0, GEMV_EDGE = 1, GEMV_INNER = 2;
 struct GemvChunk {
-  int32_t item, row0, nrows, pad;
+  int32_t item, row0, nrows, kind;
 };
 
 // One cluster of a sweep over a level l >= 1 (k_level): of its m unknowns
@@ -182,7 +199,8 @@ struct LevelTask {
   int32_t pad;
 };
 
-// Pull group: out[oslot[r]] = base[oslot[r]] + alpha * sum_items op(B_i) in[islot_i[c]].
+// Pull group: out[oslot[r]] = base[oslot[r]] + alpha * sum_items op(B_i) in[islot_i[c]]
+// (base null: zero).
 struct PullItem {
   const void *B;
   const int32_t *islot;
@@ -289,12 +307,14 @@ int elim_block_max_n(FType t);
 int elim_block_width(FType t, int n);
 int launch_elim_block(FType t, const ElimDesc *d_items, int nactive, int k0, int mode, int nmax,
                       int bw, int *d_flag, hipStream_t st);
-// out[j, c] = src[piv[j], colperm ? pinv[c] : c + col_off]
+// out[j, c] = src[piv[j], colperm ? pinv[c] : c + col_off]; with sto (needs
+// colperm) row and column x go to place sto[x / b] b + x % b instead
 struct RowGatherDesc {
   const void *src;
   void *dst;
   const int32_t *piv;
-  int32_t n, cols, lds, ldd, col_off, colperm;
+  const int32_t *sto;
+  int32_t n, cols, lds, ldd, col_off, colperm, b, pad;
 };
 int launch_row_gather(FType t, const RowGatherDesc *d_items, int n, int max_rows, hipStream_t st);
 int launch_schur_elem(FType t, int bs, const SchurGroup *d_groups, int ngroups,
@@ -329,7 +349,8 @@ struct ZeroDesc {
 };
 int launch_zero(FType t, const ZeroDesc *d_items, int n, int64_t max_elems, hipStream_t st);
 int launch_gemv(FType t, const GemvDesc *d_items, const GemvChunk *d_chunks, int nchunks,
-                const double *in, double *out, hipStream_t st);
+                const double *in, const double *corr, const double *add, double *out,
+                hipStream_t st);
 constexpr int LEVEL_CAP = 2048;      // staged inputs of one batch of items
 constexpr int LEVEL_MAXIT = 32;      // items of one batch
 // LDS of one workgroup of nt threads: inputs of a batch (twice where the

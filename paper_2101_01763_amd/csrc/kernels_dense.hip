@@ -419,8 +419,8 @@ constexpr int COPY_ILP = 8;
 template <typename Ts, typename Td>
 __global__ __launch_bounds__(256) void k_copy(const CopyDesc *__restrict__ items) {
   const CopyDesc d = items[blockIdx.x];
-  const Ts *src = (const Ts *)d.src;
-  Td *dst = (Td *)d.dst;
+  const Ts *src = gmem<const Ts>(d.src);
+  Td *dst = gmem<Td>(d.dst);
   const int64_t total = (int64_t)d.rows * d.cols;
   const Ts sc = Ts(d.scale);
   constexpr int PER = 256 * COPY_ILP;
@@ -481,8 +481,8 @@ int launch_copy(FType t, int src_is_factor, const CopyDesc *d_items, int n, int6
 template <typename Td>
 __global__ __launch_bounds__(256) void k_bsr_gather(const GatherItem *__restrict__ items, int b) {
   const GatherItem it = items[blockIdx.x];
-  const double *s = it.src;
-  Td *d = (Td *)it.dst;
+  const double *s = gmem<const double>(it.src);
+  Td *d = gmem<Td>(it.dst);
   const int bb = b * b;
   for (int idx = threadIdx.x; idx < bb; idx += 256) {
     const int r = idx / b, c = idx - r * b;
@@ -510,8 +510,8 @@ __global__ __launch_bounds__(256) void k_copy_t(const CopyDesc *__restrict__ ite
   const int r0 = tr * 64, c0 = tc * 64;
   if (r0 >= d.rows || c0 >= d.cols) return;
   __shared__ Ts tile[64][65];
-  const Ts *src = (const Ts *)d.src;
-  Td *dst = (Td *)d.dst;
+  const Ts *src = gmem<const Ts>(d.src);
+  Td *dst = gmem<Td>(d.dst);
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;    // 64 x 4
   Ts v[16];
 #pragma unroll
@@ -550,9 +550,9 @@ int launch_copy_t(FType t, int src_is_factor, const CopyDesc *d_items, int n, in
 template <typename T>
 __global__ __launch_bounds__(256) void k_scale(const ScaleDesc *__restrict__ items) {
   const ScaleDesc d = items[blockIdx.x];
-  T *A = (T *)d.A;
-  const T *rs = (const T *)d.rs;
-  const T *cs = (const T *)d.cs;
+  T *A = gmem<T>(d.A);
+  const T *rs = gmem<const T>(d.rs);
+  const T *cs = gmem<const T>(d.cs);
   const int64_t total = (int64_t)d.rows * d.cols;
   for (int64_t idx = (int64_t)blockIdx.y * blockDim.x + threadIdx.x; idx < total;
        idx += (int64_t)gridDim.y * blockDim.x) {
@@ -578,7 +578,7 @@ int launch_scale(FType t, const ScaleDesc *d_items, int n, hipStream_t st) {
 template <typename T>
 __global__ __launch_bounds__(256) void k_eye(const EyeDesc *__restrict__ items) {
   const EyeDesc d = items[blockIdx.x];
-  T *A = (T *)d.A;
+  T *A = gmem<T>(d.A);
   const int64_t total = (int64_t)d.n * d.n;
   for (int64_t idx = (int64_t)blockIdx.y * blockDim.x + threadIdx.x; idx < total;
        idx += (int64_t)gridDim.y * blockDim.x) {
@@ -590,7 +590,7 @@ __global__ __launch_bounds__(256) void k_eye(const EyeDesc *__restrict__ items) 
 template <typename T>
 __global__ __launch_bounds__(256) void k_zero(const ZeroDesc *__restrict__ items) {
   const ZeroDesc d = items[blockIdx.x];
-  T *A = (T *)d.A;
+  T *A = gmem<T>(d.A);
   const int64_t total = (int64_t)d.rows * d.cols;
   for (int64_t idx = (int64_t)blockIdx.y * blockDim.x + threadIdx.x; idx < total;
        idx += (int64_t)gridDim.y * blockDim.x) {
@@ -647,9 +647,9 @@ __global__ __launch_bounds__(ELIM_NT) void k_elim_panel(const ElimDesc *__restri
   const int n = d.n;
   if (k >= n) return;
   const int w = min(NB, n - k);
-  T *A = (T *)d.A;
-  T *P = (T *)d.P;
-  T *Tb = (T *)d.T;
+  T *A = gmem<T>(d.A);
+  T *P = gmem<T>(d.P);
+  T *Tb = gmem<T>(d.T);
   const int64_t ld = d.ld;
   const int tid = threadIdx.x;
   __shared__ T prow_s[NB];
@@ -674,7 +674,7 @@ __global__ __launch_bounds__(ELIM_NT) void k_elim_panel(const ElimDesc *__restri
 #pragma unroll
       for (int c = 0; c < NB; ++c)
         if (c < w) pan[j][c] = A[(int64_t)r * ld + k + c];
-      if (MODE != 2) usedf[j] = d.used[r] != 0;
+      if (MODE != 2) usedf[j] = gmem<int32_t>(d.used)[r] != 0;
     }
   }
 #pragma unroll
@@ -772,9 +772,9 @@ __global__ __launch_bounds__(ELIM_NT) void k_elim_panel(const ElimDesc *__restri
       if (cc < w) A[(int64_t)r * ld + k + cc] = pan[j][cc];
       P[(int64_t)r * NB + cc] = (cc < w) ? (MODE == 1 ? Y[j][cc] : pan[j][cc]) : T(0);
     }
-    if (MODE != 2) d.used[r] = usedf[j] ? 1 : 0;
+    if (MODE != 2) gmem<int32_t>(d.used)[r] = usedf[j] ? 1 : 0;
   }
-  if (tid < w) d.piv[k + tid] = s_piv[tid];
+  if (tid < w) gmem<int32_t>(d.piv)[k + tid] = s_piv[tid];
   // pivot rows of the non-panel columns -> T, then zero them in A.  The
   // panel columns of T are zero so the update leaves the panel unchanged.
   // Only the column window [cw0, cw1) is touched (a blocked elimination
@@ -812,9 +812,9 @@ __global__ __launch_bounds__(256) void k_elim_update(const ElimDesc *__restrict_
   const int m0 = (t / ntn) * 64, n0 = c0 + (t % ntn) * 64;
   __shared__ T Ps[ELIM_NB][65];
   __shared__ T Ts[ELIM_NB][65];
-  const T *P = (const T *)d.P;
-  const T *Tb = (const T *)d.T;
-  T *A = (T *)d.A;
+  const T *P = gmem<const T>(d.P);
+  const T *Tb = gmem<const T>(d.T);
+  T *A = gmem<T>(d.A);
   const int64_t ld = d.ld;
   const int tid = threadIdx.x;
   for (int idx = tid; idx < ELIM_NB * 64; idx += 256) {
@@ -965,7 +965,7 @@ __global__ __launch_bounds__(MAXT) void k_elim_block(const ElimDesc *__restrict_
   const int wb = min(BW, n - k0);          // columns eliminated
   const int wc = min(BW, d.ncols - k0);    // columns of the window carried along
   const int tid = threadIdx.x, wv = tid >> 6, nw = blockDim.x >> 6;
-  T *A = (T *)d.A;
+  T *A = gmem<T>(d.A);
   const int64_t ld = d.ld;
   __shared__ __align__(16) T cand[2][NWMAX][BW];
   __shared__ uint64_t cval[2][NWMAX];
@@ -995,7 +995,7 @@ __global__ __launch_bounds__(MAXT) void k_elim_block(const ElimDesc *__restrict_
       for (int i = 0; i < BW; ++i)
         if (i < wc) s[i] = src[i];
     }
-    if (!NOPIV && d.used[tid] != 0) {
+    if (!NOPIV && gmem<int32_t>(d.used)[tid] != 0) {
       used = true;
       pc = -2;
     }
@@ -1076,7 +1076,7 @@ __global__ __launch_bounds__(MAXT) void k_elim_block(const ElimDesc *__restrict_
     if (MODE == 3) {
       // shifted pivot a_cc - s_c with s_c = -sign(a_cc): modulus >= 1
       const T sgn = p >= T(0) ? T(-1) : T(1);
-      if (tid == 0) ((T *)d.sg)[k0 + c] = sgn;
+      if (tid == 0) (gmem<T>(d.sg))[k0 + c] = sgn;
       p -= sgn;
     } else if (p == T(0)) {
       if (tid == 0) atomicOr(flag, 1);
@@ -1134,7 +1134,7 @@ __global__ __launch_bounds__(MAXT) void k_elim_block(const ElimDesc *__restrict_
   if (live) {
     T *dst = A + (int64_t)tid * ld + k0;
     if (MODE == 1) {
-      T *pb = (T *)d.PB + (int64_t)tid * BW;
+      T *pb = gmem<T>(d.PB) + (int64_t)tid * BW;
 #pragma unroll
       for (int i = 0; i < BW; ++i) {
         const int col = (nsteps + i) & (BW - 1);
@@ -1172,9 +1172,9 @@ __global__ __launch_bounds__(MAXT) void k_elim_block(const ElimDesc *__restrict_
         if (col < wc) dst[col] = s[i];
       }
     }
-    if (!NOPIV) d.used[tid] = used ? 1 : 0;
+    if (!NOPIV) gmem<int32_t>(d.used)[tid] = used ? 1 : 0;
   }
-  if (tid < wb) d.piv[k0 + tid] = s_piv[tid];
+  if (tid < wb) gmem<int32_t>(d.piv)[k0 + tid] = s_piv[tid];
 }
 
 int elim_block_max_n(FType) { return 1024; }
@@ -1228,11 +1228,11 @@ __global__ __launch_bounds__(256) void k_elim_extract(const ElimDesc *__restrict
   if (k0 >= d.n) return;
   const int wb = min(bw, d.n - k0);
   const int cw1 = k0 + bw;
-  T *A = (T *)d.A;
-  T *TB = (T *)d.TB;
+  T *A = gmem<T>(d.A);
+  T *TB = gmem<T>(d.TB);
   const int64_t ld = d.ld;
   for (int q = blockIdx.y; q < wb; q += gridDim.y) {
-    T *__restrict__ row = A + (int64_t)d.piv[k0 + q] * ld;
+    T *__restrict__ row = A + (int64_t)gmem<int32_t>(d.piv)[k0 + q] * ld;
     T *__restrict__ tb = TB + (int64_t)q * ld;
     // four loads in flight per thread before the stores
     for (int c0 = threadIdx.x; c0 < d.ncols; c0 += 4 * 256) {
@@ -1277,19 +1277,19 @@ __global__ __launch_bounds__(256) void k_elim_pb(const ElimDesc *__restrict__ it
   if (k >= d.n) return;
   const int w = min(ELIM_NB, d.n - k);
   const int c1 = k - k0;                   // columns of earlier panels in PB
-  const T *Y = (const T *)d.P;
-  T *PB = (T *)d.PB;
+  const T *Y = gmem<const T>(d.P);
+  T *PB = gmem<T>(d.PB);
   __shared__ double ts[ELIM_NB * ELIM_BLK];
   const int tid = threadIdx.x;
   if (c1 > 0) {
     for (int idx = tid; idx < w * c1; idx += 256) {
       const int t = idx / c1, c = idx % c1;
-      ts[idx] = double(PB[(int64_t)d.piv[k + t] * ELIM_BLK + c]);
+      ts[idx] = double(PB[(int64_t)gmem<int32_t>(d.piv)[k + t] * ELIM_BLK + c]);
     }
     __syncthreads();
     for (int idx = tid; idx < w * c1; idx += 256) {
       const int t = idx / c1, c = idx % c1;
-      PB[(int64_t)d.piv[k + t] * ELIM_BLK + c] = T(0);
+      PB[(int64_t)gmem<int32_t>(d.piv)[k + t] * ELIM_BLK + c] = T(0);
     }
     __syncthreads();
     for (int idx = tid; idx < d.n * c1; idx += 256) {
@@ -1320,15 +1320,20 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_row_gather(const RowGatherDesc *__restrict__ items) {
   const RowGatherDesc d = items[blockIdx.x];
   __shared__ int pinv[ELIM_MAXN];
+  auto sto = [&](int x) {
+    if (!d.sto) return x;
+    const int e = x / d.b;
+    return gmem<int32_t>(d.sto)[e] * d.b + x - e * d.b;
+  };
   if (d.colperm) {
-    for (int j = threadIdx.x; j < d.n; j += blockDim.x) pinv[d.piv[j]] = j;
+    for (int j = threadIdx.x; j < d.n; j += blockDim.x) pinv[sto(gmem<int32_t>(d.piv)[j])] = j;
   }
   __syncthreads();
-  const T *src = (const T *)d.src;
-  T *dst = (T *)d.dst;
+  const T *src = gmem<const T>(d.src);
+  T *dst = gmem<T>(d.dst);
   for (int j = blockIdx.y; j < d.n; j += gridDim.y) {
-    const T *srow = src + (int64_t)d.piv[j] * d.lds;
-    T *drow = dst + (int64_t)j * d.ldd;
+    const T *srow = src + (int64_t)gmem<int32_t>(d.piv)[j] * d.lds;
+    T *drow = dst + (int64_t)sto(j) * d.ldd;
     // four loads in flight per thread before the stores
     for (int c0 = threadIdx.x; c0 < d.cols; c0 += 4 * 256) {
       T v[4];
@@ -1371,7 +1376,7 @@ __global__ __launch_bounds__(256, 4) void k_schur_elem_mfma(int bs, const SchurG
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int wr = wid >> 1, wc = wid & 1;
   const int kmax = (bs + 1) & ~1;
-  float *tg = (float *)g.target;
+  float *tg = gmem<float>(g.target);
   const int col = wc * 32 + (lane & 31);
   f32x16 acc;
 #pragma unroll
@@ -1392,8 +1397,8 @@ __global__ __launch_bounds__(256, 4) void k_schur_elem_mfma(int bs, const SchurG
   float ra[NE], ry[NE], r2[NE];
   auto fetch_a1y = [&](int it) {
     const SchurItem s = items[it];
-    const float *a1 = (const float *)s.A1 + r0 * bs + c0;
-    const float *Y = (const float *)s.Y + (int64_t)r0 * s.ldy + c0;
+    const float *a1 = gmem<const float>(s.A1) + r0 * bs + c0;
+    const float *Y = gmem<const float>(s.Y) + (int64_t)r0 * s.ldy + c0;
     const int64_t ys = 4 * (int64_t)s.ldy;
 #pragma unroll
     for (int q = 0; q < NE; ++q)
@@ -1403,7 +1408,7 @@ __global__ __launch_bounds__(256, 4) void k_schur_elem_mfma(int bs, const SchurG
       }
   };
   auto fetch_a2 = [&](int it) {
-    const float *a2 = (const float *)items[it].A2 + r0 * bs + c0;
+    const float *a2 = gmem<const float>(items[it].A2) + r0 * bs + c0;
 #pragma unroll
     for (int q = 0; q < NE; ++q)
       if (cin && r0 + 4 * q < bs) r2[q] = a2[q * 4 * bs];
@@ -1466,7 +1471,7 @@ __global__ __launch_bounds__(256, 2) void k_schur_elem_mfma64(int bs, const Schu
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int wr = wid >> 1, wc = wid & 1;
   const int kmax = (bs + 3) & ~3;
-  double *tg = (double *)g.target;
+  double *tg = gmem<double>(g.target);
   f64x4 acc[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -1490,8 +1495,8 @@ __global__ __launch_bounds__(256, 2) void k_schur_elem_mfma64(int bs, const Schu
   double ra[NE], ry[NE], r2[NE];
   auto fetch_a1y = [&](int it) {
     const SchurItem s = items[it];
-    const double *a1 = (const double *)s.A1 + r0 * bs + c0;
-    const double *Y = (const double *)s.Y + (int64_t)r0 * s.ldy + c0;
+    const double *a1 = gmem<const double>(s.A1) + r0 * bs + c0;
+    const double *Y = gmem<const double>(s.Y) + (int64_t)r0 * s.ldy + c0;
     const int64_t ys = 4 * (int64_t)s.ldy;
 #pragma unroll
     for (int q = 0; q < NE; ++q)
@@ -1501,7 +1506,7 @@ __global__ __launch_bounds__(256, 2) void k_schur_elem_mfma64(int bs, const Schu
       }
   };
   auto fetch_a2 = [&](int it) {
-    const double *a2 = (const double *)items[it].A2 + r0 * bs + c0;
+    const double *a2 = gmem<const double>(items[it].A2) + r0 * bs + c0;
 #pragma unroll
     for (int q = 0; q < NE; ++q)
       if (cin && r0 + 4 * q < bs) r2[q] = a2[q * 4 * bs];
@@ -1678,12 +1683,12 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
   constexpr int VN = 16 / sizeof(T);            // columns per 16-byte load
   using VT = typename std::conditional<sizeof(T) == 4, float4, double2>::type;
   const int ngrp = (nc + VN - 1) / VN;
-  const T *W = (const T *)d.W;      // current layout (packed copies alternate with W2)
-  T *Wother = (T *)d.W2;
-  T *Q = (T *)d.Q;
-  T *Qt = (T *)d.V;
-  double *vn1 = d.vn1, *vn2 = d.vn2;
-  int *sel = d.sel;
+  const T *W = gmem<const T>(d.W);      // current layout (packed copies alternate with W2)
+  T *Wother = gmem<T>(d.W2);
+  T *Q = gmem<T>(d.Q);
+  T *Qt = gmem<T>(d.V);
+  double *vn1 = gmem<double>(d.vn1), *vn2 = gmem<double>(d.vn2);
+  int *sel = gmem<int>(d.sel);
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   // dynamic LDS: u[MS], cbuf[MS] (or the two GEMM tiles, or the
   // candidates' coefficients P[MS][BQ]), the candidate
@@ -1695,7 +1700,7 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
   double *Bm = qsm + ldsd, *Cc = Bm + BQ * MS, *av = Cc + BQ * BQ;
   int *act = reinterpret_cast<int *>(av + BQ);
   int *sidx = act + GS;
-  double *H = d.H;                  // ldw x BQ: column j of B W at H + j BQ
+  double *H = gmem<double>(d.H);                  // ldw x BQ: column j of B W at H + j BQ
   __shared__ int s_j, s_nflag, s_nf, s_in;
   __shared__ double rv[4];
   __shared__ int ri[4];
@@ -2462,9 +2467,9 @@ namespace spand {
 template <typename T>
 __global__ void k_diag_split(const DiagDesc *__restrict__ items) {
   const DiagDesc d = items[blockIdx.x];
-  const T *U = (const T *)d.U;
-  T *S = (T *)d.S;
-  T *Si = (T *)d.Si;
+  const T *U = gmem<const T>(d.U);
+  T *S = gmem<T>(d.S);
+  T *Si = gmem<T>(d.Si);
   for (int j = threadIdx.x; j < d.n; j += blockDim.x) {
     const T s = sqrt(fabs(U[(int64_t)j * d.ld + j]));
     S[j] = s;

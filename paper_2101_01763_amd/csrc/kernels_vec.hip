@@ -18,6 +18,13 @@ __device__ inline T wsum(T v) {
 
 // ------------------------------------------------------------------ GEMV
 // out[oslot[r]] = sum_c op(A)(r, c) in[islot[c]]   (level 0 of the sweeps)
+// Bound by HBM: the leaf inverses are most of the bytes of an apply, and the
+// two sweeps need only parts of them.  Only a leaf's unknowns next to a
+// separator (0:nb) couple to anything: the forward sweep needs just their
+// rows of t = A_ss^-1 x_s, and with the couplings' correction c on them the
+// backward sweep's A_ss^-1 (x_s + c) is t + A_ss^-1 c on those rows, a product
+// with nb columns.  So n^2 + nb^2 elements are read instead of 2 n^2 (measured
+// at Factor::sweeps).
 // One workgroup per band of output rows (GemvChunk).  The input is staged
 // in LDS.  Bands of one item may run concurrently, so in == out is not
 // allowed (the sweeps alternate between two vectors).
@@ -46,17 +53,29 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_gemv(const GemvDesc *__restrict__ items,
                                               const GemvChunk *__restrict__ chunks,
                                               const double *__restrict__ in,
+                                              const double *__restrict__ corr,
+                                              const double *__restrict__ add,
                                               double *__restrict__ out) {
   using VW = Vec16<T>;
   constexpr int VN = VW::N;
   const GemvChunk ch = chunks[blockIdx.x];
-  const GemvDesc d = items[ch.item];
+  GemvDesc d = items[ch.item];
   __shared__ double xs[GEMV_MAXC];
   __shared__ double part[256];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  for (int c = tid; c < d.cols; c += 256) xs[c] = in[d.islot[c]];
+  if (ch.kind == GEMV_EDGE) d.cols = d.nb;
+  for (int c = tid; c < d.cols; c += 256) {
+    const int s = gmem<const int32_t>(d.islot)[c];
+    double v = ch.kind == GEMV_EDGE ? corr[s] : in[s];
+    if (ch.kind == GEMV_INNER && c < d.nb) v += corr[s];
+    xs[c] = v;
+  }
   __syncthreads();
-  const T *A = (const T *)d.A;
+  auto put = [&](int r, double v) {
+    const int o = gmem<const int32_t>(d.oslot)[r];
+    out[o] = ch.kind == GEMV_EDGE ? add[o] + v : v;
+  };
+  const T *A = gmem<const T>(d.A);
   if (!d.trans) {
     // each wave works on four rows at once (independent sums keep four
     // rows' loads in flight); rows past the band re-read the band's last
@@ -89,7 +108,7 @@ __global__ __launch_bounds__(256) void k_gemv(const GemvDesc *__restrict__ items
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           if (rr0 + q >= ch.nrows) break;
-          out[d.oslot[ch.row0 + rr0 + q]] = acc[q];
+          put(ch.row0 + rr0 + q, acc[q]);
         }
     }
   } else {
@@ -110,17 +129,20 @@ __global__ __launch_bounds__(256) void k_gemv(const GemvDesc *__restrict__ items
     part[tid] = a;
     __syncthreads();
     if (tid < ch.nrows)
-      out[d.oslot[ch.row0 + tid]] = (part[tid] + part[tid + 64]) + (part[tid + 128] + part[tid + 192]);
+      put(ch.row0 + tid, (part[tid] + part[tid + 64]) + (part[tid + 128] + part[tid + 192]));
   }
 }
 
 int launch_gemv(FType t, const GemvDesc *d_items, const GemvChunk *d_chunks, int nchunks,
-                const double *in, double *out, hipStream_t st) {
+                const double *in, const double *corr, const double *add, double *out,
+                hipStream_t st) {
   if (nchunks <= 0) return SPAND_OK;
   if (t == FType::F64)
-    hipLaunchKernelGGL(k_gemv<double>, dim3(nchunks), dim3(256), 0, st, d_items, d_chunks, in, out);
+    hipLaunchKernelGGL(k_gemv<double>, dim3(nchunks), dim3(256), 0, st, d_items, d_chunks, in,
+                       corr, add, out);
   else
-    hipLaunchKernelGGL(k_gemv<float>, dim3(nchunks), dim3(256), 0, st, d_items, d_chunks, in, out);
+    hipLaunchKernelGGL(k_gemv<float>, dim3(nchunks), dim3(256), 0, st, d_items, d_chunks, in,
+                       corr, add, out);
   SP_HIP(hipGetLastError());
   return SPAND_OK;
 }
@@ -144,8 +166,6 @@ int launch_gemv(FType t, const GemvDesc *d_items, const GemvChunk *d_chunks, int
 // couplings of a cluster accumulate in item order.
 constexpr int LEVEL_LANES = 8;
 
-// Matrices are addressed as global memory (the pointers come out of LDS, from
-// which the compiler cannot tell).
 template <typename T>
 using GPtr = const T __attribute__((address_space(1))) *;
 template <typename T>
@@ -392,9 +412,9 @@ __global__ __launch_bounds__(256) void k_pull(const PullGroup *__restrict__ grou
   for (int it = g.item_begin; it < g.item_end; ++it) {
     const PullItem p = items[it];
     __syncthreads();
-    for (int c = tid; c < p.cols; c += 256) xs[c] = in[p.islot[c]];
+    for (int c = tid; c < p.cols; c += 256) xs[c] = in[gmem<const int32_t>(p.islot)[c]];
     __syncthreads();
-    const T *B = (const T *)p.B;
+    const T *B = gmem<const T>(p.B);
     if (!TRANS) {
       // 4 lanes per row, 16-byte loads from the row's first 16-byte
       // boundary on (a row of any leading dimension: the few elements
@@ -436,8 +456,8 @@ __global__ __launch_bounds__(256) void k_pull(const PullGroup *__restrict__ grou
     }
   }
   auto put = [&](int r, double v) {
-    const int o = g.oslot[ch.row0 + r];
-    out[o] = base[o] + alpha * v;
+    const int o = gmem<const int32_t>(g.oslot)[ch.row0 + r];
+    out[o] = (base ? base[o] : 0.0) + alpha * v;
   };
   if (!TRANS) {
     const int rr = tid >> 2;
