@@ -885,14 +885,21 @@ int launch_elim_step(FType t, const ElimDesc *d_items, int nactive, int k, int m
 // Largest of v over the 64 lanes of a wave (every lane active), in every
 // lane: DPP max within each row of 16 (quad xor 1, quad xor 2, half-row
 // mirror, row mirror), then the four row results through readlane.
+__device__ inline uint32_t row16_max_u32(uint32_t v);
 __device__ inline uint32_t wave_max_u32(uint32_t v) {
+  v = row16_max_u32(v);
+  const uint32_t a = __builtin_amdgcn_readlane((int)v, 0), b = __builtin_amdgcn_readlane((int)v, 16);
+  const uint32_t c = __builtin_amdgcn_readlane((int)v, 32), d = __builtin_amdgcn_readlane((int)v, 48);
+  return max(max(a, b), max(c, d));
+}
+
+// Largest of v over each row of 16 lanes, in every lane of the row.
+__device__ inline uint32_t row16_max_u32(uint32_t v) {
   v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false));
   v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false));
   v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false));
   v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, false));
-  const uint32_t a = __builtin_amdgcn_readlane((int)v, 0), b = __builtin_amdgcn_readlane((int)v, 16);
-  const uint32_t c = __builtin_amdgcn_readlane((int)v, 32), d = __builtin_amdgcn_readlane((int)v, 48);
-  return max(max(a, b), max(c, d));
+  return v;
 }
 
 // Pivot key of a value: the bit pattern of |x| orders like |x| (NaN counts
@@ -927,20 +934,87 @@ __device__ inline int wave_argmax_key(uint64_t key, bool can, uint64_t *kmax) {
 }
 
 // ------------------------------------------------------------------ fused block elimination
+// s[0..7] += h * p_l for the lanes l = R..R+7 of every row of 16 lanes of p:
+// a value that the lanes of a wave hold once per 16 lanes multiplies every
+// lane's h without a trip through LDS (DPP row_newbcast).  The wait states
+// cover a p that was computed right before.
+template <int R>
+__device__ inline void fmac8(float *s, float p, float h) {
+  static_assert(R == 0 || R == 8, "half rows");
+#define FMAC_ROW(i, l) "v_fmac_f32_dpp %" #i ", %8, %9 row_newbcast:" #l " row_mask:0xf bank_mask:0xf\n\t"
+  if constexpr (R == 0)
+    asm("s_nop 1\n\t" FMAC_ROW(0, 0) FMAC_ROW(1, 1) FMAC_ROW(2, 2) FMAC_ROW(3, 3) FMAC_ROW(4, 4)
+            FMAC_ROW(5, 5) FMAC_ROW(6, 6) FMAC_ROW(7, 7)
+        : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7])
+        : "v"(p), "v"(h));
+  else
+    asm("s_nop 1\n\t" FMAC_ROW(0, 8) FMAC_ROW(1, 9) FMAC_ROW(2, 10) FMAC_ROW(3, 11) FMAC_ROW(4, 12)
+            FMAC_ROW(5, 13) FMAC_ROW(6, 14) FMAC_ROW(7, 15)
+        : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7])
+        : "v"(p), "v"(h));
+#undef FMAC_ROW
+}
+template <int R>
+__device__ inline void fmac8(double *s, double p, double h) {
+  static_assert(R == 0 || R == 8, "half rows");
+#define FMAC_ROW(i, l) "v_fmac_f64_dpp %" #i ", %8, %9 row_newbcast:" #l " row_mask:0xf bank_mask:0xf\n\t"
+  if constexpr (R == 0)
+    asm("s_nop 1\n\t" FMAC_ROW(0, 0) FMAC_ROW(1, 1) FMAC_ROW(2, 2) FMAC_ROW(3, 3) FMAC_ROW(4, 4)
+            FMAC_ROW(5, 5) FMAC_ROW(6, 6) FMAC_ROW(7, 7)
+        : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7])
+        : "v"(p), "v"(h));
+  else
+    asm("s_nop 1\n\t" FMAC_ROW(0, 8) FMAC_ROW(1, 9) FMAC_ROW(2, 10) FMAC_ROW(3, 11) FMAC_ROW(4, 12)
+            FMAC_ROW(5, 13) FMAC_ROW(6, 14) FMAC_ROW(7, 15)
+        : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7])
+        : "v"(p), "v"(h));
+#undef FMAC_ROW
+}
+// the same for the four lanes 4..7
+__device__ inline void fmac4(float *s, float p, float h) {
+#define FMAC_ROW(i, l) "v_fmac_f32_dpp %" #i ", %4, %5 row_newbcast:" #l " row_mask:0xf bank_mask:0xf\n\t"
+  asm("s_nop 1\n\t" FMAC_ROW(0, 4) FMAC_ROW(1, 5) FMAC_ROW(2, 6) FMAC_ROW(3, 7)
+      : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]) : "v"(p), "v"(h));
+#undef FMAC_ROW
+}
+__device__ inline void fmac4(double *s, double p, double h) {
+#define FMAC_ROW(i, l) "v_fmac_f64_dpp %" #i ", %4, %5 row_newbcast:" #l " row_mask:0xf bank_mask:0xf\n\t"
+  asm("s_nop 1\n\t" FMAC_ROW(0, 4) FMAC_ROW(1, 5) FMAC_ROW(2, 6) FMAC_ROW(3, 7)
+      : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]) : "v"(p), "v"(h));
+#undef FMAC_ROW
+}
+
 // One workgroup eliminates the block columns [k0, k0 + wb), wb <= BW, of
 // one matrix and applies them to the whole column window [k0, k0 + BW)
 // (columns past n exist for LU on [A | I]); one row per thread
 // (blockDim.x >= n), the window part of the row in registers.  BW = 64
 // (ELIM_BLK), except for FP64 matrices of more than 512 rows: 1024 rows of
 // 64 doubles would take the whole register file of a CU, so they take
-// blocks of 32 columns.  The
-// steps run in groups of 4 columns with the slots fixed inside a group, so
-// every register index is a compile-time constant while the group loop
-// stays rolled (see the step below).
-// Per step: argmax of |a_rc| over the rows that may still pivot (DPP wave
-// maximum and ballot, ties to the lowest row; each wave posts its
-// candidate's whole row to LDS and one barrier later every thread takes
-// the best), then one fused multiply-add per slot.
+// blocks of 32 columns.
+//
+// The columns go in panels of 4.  Inside a panel each step touches the
+// panel's 4 slots only: argmax of |a_rc| over the rows that may still pivot
+// (DPP wave maximum and ballot, ties to the lowest row; each wave posts its
+// candidate's 4 values, one barrier later every thread takes the best), then
+// 4 multiply-adds.  The rows chosen as pivots leave their whole window part,
+// as it was before the panel, in LDS.  After the panel's one further barrier
+// every wave brings those 4 rows up to date itself (lane l holds slots
+// l % 16 + 16 q) and applies them to its own rows' other slots, each value
+// broadcast across the lanes inside the multiply-add.  Without pivoting the
+// panel's rows are known beforehand and one barrier per panel is left.  Every
+// slot sees the same multiply-adds in the same order as with one whole-row
+// update per step, which is the method's definition.
+//   Bound by the latency of a step's chain (wave maximum 120 cycles, two trips
+// through LDS 75 each, division 65, ...: about 0.4 us a step of a single
+// wave) and by the slots' multiply-adds (64 of 4.6 cycles per wave and step).
+// One workgroup of 1024 threads, FP64, 32 columns: 106 -> 63 us; 3906 FP32
+// matrices of 576 rows, 64 columns: 2.10 -> 1.63 ms; LU of 4128 of 256 rows:
+// 1.68 -> 0.68 ms (of it 0.9 ms by writing the LU's two row parts as 16-byte
+// vectors).  Before, every step carried whole rows through LDS (each wave's
+// candidate written, the pivot row read back by every lane).  Two panels of
+// code per trip round the loop (no slot rotation between them) were slower
+// (instruction fetch), and so was a bound of 96 registers for a second
+// workgroup per compute unit (spills: 1.85 ms).
 //   MODE 0/2: Gauss-Jordan (with / without pivoting); every row changes,
 //             the pivot row is scaled; on exit the block columns are the
 //             block's P_B.
@@ -958,19 +1032,20 @@ __global__ __launch_bounds__(MAXT) void k_elim_block(const ElimDesc *__restrict_
                                                      int *__restrict__ flag) {
   constexpr int NWMAX = MAXT / 64, V = 16 / sizeof(T);
   constexpr bool NOPIV = MODE >= 2;        // pivot of block column c is row k0 + c
-  static_assert(BW >= 8 && (BW & (BW - 1)) == 0, "slot rotation needs a power-of-two block");
+  static_assert(BW % 16 == 0 && (BW & (BW - 1)) == 0, "slot rotation needs a power-of-two block");
   const ElimDesc d = items[blockIdx.x];
   const int n = d.n;
   if (k0 >= n) return;
   const int wb = min(BW, n - k0);          // columns eliminated
   const int wc = min(BW, d.ncols - k0);    // columns of the window carried along
-  const int tid = threadIdx.x, wv = tid >> 6, nw = blockDim.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6;
   T *A = gmem<T>(d.A);
   const int64_t ld = d.ld;
-  __shared__ __align__(16) T cand[2][NWMAX][BW];
+  __shared__ __align__(16) T cand[2][NWMAX][4];
+  __shared__ __align__(16) T prow_s[2][4][BW];   // pivot rows of a panel, as before it
+  __shared__ __align__(16) T hm_s[2][4][4];      // their multipliers at the panel's earlier steps
   __shared__ uint64_t cval[2][NWMAX];
   __shared__ int cidx[2][NWMAX];
-  __shared__ unsigned long long ckey[3];   // FP32: (|pivot| bits << 32) | ~row, max over waves
   __shared__ int s_piv[BW];
   const bool live = tid < n;
   // 16-byte row chunks when every row start is aligned and the block is whole
@@ -1000,127 +1075,200 @@ __global__ __launch_bounds__(MAXT) void k_elim_block(const ElimDesc *__restrict_
       pc = -2;
     }
   }
-  constexpr bool KEYED = sizeof(T) == 4 && !NOPIV;
-  if (KEYED) {
-    if (tid < 3) ckey[tid] = 0;
-    __syncthreads();
-  }
-  // One step per block column.  The steps run in groups of 4: at the start
-  // of a group slot i holds block column (c0 + i) mod BW, step k of the
-  // group eliminates slot k (a compile-time index), and the slots rotate by
-  // 4 between groups.  Inside a group every slot stays in its register, so
-  // the candidate rows go to LDS and come back as aligned 16-byte vectors.
-  auto step = [&](const int c, const int k) {
-    if (c >= wb) return;
+  auto fail = [&]() {          // reported as a failed factorization
+    if (tid == 0) *flag = 1;
+  };
+  // the pivot of step c (panel slot value x): row and, through ws, the wave
+  // whose candidate it is; post(): this thread is its wave's candidate
+  auto find_pivot = [&](int c, T x, int &ws, auto post) {
     const int buf = c & 1;
-    int prow, ws = 0, bi = -1;
     uint64_t kmax = 0;
-    if (NOPIV) {
+    const int wl = wave_argmax_key<T>(pivot_key(x), live && !used, &kmax);
+    if (lane == wl) post();
+    if (lane == 0) {
+      cval[buf][wv] = kmax;
+      cidx[buf][wv] = wl;
+    }
+    __syncthreads();
+    // best candidate over the (at most 16) waves, one per lane, the same in
+    // every row of 16 lanes; on equal keys the lower wave holds the lower row
+    const int l = lane & 15;
+    const uint64_t kq = l < nw ? cval[buf][l] : 0;
+    const int iq = l < nw ? cidx[buf][l] : -1;
+    uint64_t b;
+    if (sizeof(T) == 4) {
+      const uint32_t q = uint32_t(kq), m = row16_max_u32(iq >= 0 ? q : 0u);
+      b = __ballot(iq >= 0 && q == m);
+    } else {
+      const uint32_t hi = uint32_t(kq >> 32), lo = uint32_t(kq);
+      const uint32_t mh = row16_max_u32(iq >= 0 ? hi : 0u);
+      const bool c1 = iq >= 0 && hi == mh;
+      const uint32_t ml = row16_max_u32(c1 ? lo : 0u);
+      b = __ballot(c1 && lo == ml);
+    }
+    int prow = -1;
+    ws = 0;
+    if (b) {
+      ws = int(__builtin_ctzll(b)) & 15;
+      prow = (ws << 6) + __builtin_amdgcn_readlane(iq, ws);
+    }
+    // some row may always pivot (n - k0 - c unused rows); the fallback only
+    // keeps a bad key from naming a row out of range
+    if (prow < 0 || prow >= n) {
+      fail();
       prow = k0 + c;
-      if (tid == prow) {
-#pragma unroll
-        for (int i = 0; i < BW; i += V) *(uint4 *)&cand[buf][0][i] = *(const uint4 *)&s[i];
-      }
-      __syncthreads();
-    } else {
-      const bool can = live && !used;
-      const int wl = wave_argmax_key<T>(pivot_key(s[k]), can, &kmax);
-      bi = wl < 0 ? -1 : (wv << 6) + wl;
-      if (tid == bi) {
-#pragma unroll
-        for (int i = 0; i < BW; i += V) *(uint4 *)&cand[buf][wv][i] = *(const uint4 *)&s[i];
-      }
-      // kmax and bi are uniform over the wave
-      if (KEYED && bi >= 0 && (tid & 63) == 0)
-        atomicMax(&ckey[c % 3], (unsigned long long)((kmax << 32) | uint32_t(~bi)));
+      ws = 0;
     }
-    if (KEYED) {
-      // the key of step c - 1 is no longer read by anyone: clear it for step c + 2
+    return prow;
+  };
+  // One panel: block columns c0..c0+3 in the slots 0..3.
+  auto panel = [&](const int c0) {
+    const int g = (c0 >> 2) & 1;
+    T h[4], ip[4];
+    T hm[4][4];            // hm[k][j]: multiplier of pivot row k at step j < k
+    T G[4][4];             // without pivoting: the pivot rows' panel slots
+    int pk = -1;           // panel step this row pivots at
+    if (NOPIV) {
+      const int q = tid - (k0 + c0);
+      if (q >= 0 && q < 4) {
+#pragma unroll
+        for (int i = 0; i < BW; i += V) *(uint4 *)&prow_s[g][q][i] = *(const uint4 *)&s[i];
+      }
       __syncthreads();
-      if (tid == 0) ckey[(c + 2) % 3] = 0;
-      const unsigned long long key = ckey[c % 3];
-      prow = key ? int(~uint32_t(key)) : -1;
-      ws = prow >> 6;
-      if (prow < 0 || prow >= n) {
-        if (tid == 0) atomicOr(flag, 1);   // reported as a failed factorization
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; i += V) *(uint4 *)&G[k][i] = *(const uint4 *)&prow_s[g][k][i];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int c = c0 + k;
+      h[k] = T(0);
+      ip[k] = T(1);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (j >= k) hm[k][j] = T(0);
+      if (c >= wb) {
+#pragma unroll
+        for (int j = 0; j < k; ++j) hm[k][j] = T(0);
+        continue;
+      }
+      int prow;
+      T pr[4];
+      if (NOPIV) {
         prow = k0 + c;
-        ws = 0;
-      }
-    } else if (!NOPIV) {
-      if ((tid & 63) == 0) {
-        cval[buf][wv] = kmax;
-        cidx[buf][wv] = bi;
-      }
-      __syncthreads();
-      // best candidate over the waves; on equal keys the lower wave holds
-      // the lower row.  Some row may always pivot (n - k0 - c unused rows),
-      // the fallback only keeps a bad key from naming a row out of range.
-      uint64_t best = 0;
-      ws = -1;
-      for (int q = 0; q < nw; ++q) {
-        const uint64_t kq = cval[buf][q];
-        if (cidx[buf][q] >= 0 && (ws < 0 || kq > best)) { best = kq; ws = q; }
-      }
-      prow = ws < 0 ? -1 : cidx[buf][ws];
-      if (prow < 0 || prow >= n) {
-        if (tid == 0) atomicOr(flag, 1);   // reported as a failed factorization
-        prow = k0 + c;
-        ws = 0;
-      }
-    }
-    const uint4 *pr = (const uint4 *)&cand[buf][ws][0];
-    if (tid == 0) s_piv[c] = prow;
-    T pq[V];
-    *(uint4 *)pq = pr[k / V];
-    T p = pq[k % V];
-    if (MODE == 3) {
-      // shifted pivot a_cc - s_c with s_c = -sign(a_cc): modulus >= 1
-      const T sgn = p >= T(0) ? T(-1) : T(1);
-      if (tid == 0) (gmem<T>(d.sg))[k0 + c] = sgn;
-      p -= sgn;
-    } else if (p == T(0)) {
-      if (tid == 0) atomicOr(flag, 1);
-      p = T(1);
-    }
-    const T ip = T(1) / p;
-    const bool is_piv = tid == prow;
-    T h, z;
-    if (MODE == 1) {
-      const bool upd = live && !used && !is_piv;
-      h = upd ? -s[k] * ip : T(0);
-      z = upd ? h : s[k];
-      if (is_piv) {
-        used = true;
-        pc = c;
-      }
-    } else {
-      if (is_piv) {
 #pragma unroll
-        for (int i = 0; i < BW; ++i) s[i] *= ip;
-        h = T(0);
-        z = ip;
-        used = true;
+        for (int i = 0; i < 4; ++i) pr[i] = G[k][i];
       } else {
-        h = -s[k] * ip;
-        z = h;
+        int ws;
+        prow = find_pivot(c, s[k], ws, [&]() {
+#pragma unroll
+          for (int i = 0; i < 4; i += V) *(uint4 *)&cand[c & 1][wv][i] = *(const uint4 *)&s[i];
+        });
+#pragma unroll
+        for (int i = 0; i < 4; i += V) *(uint4 *)&pr[i] = *(const uint4 *)&cand[c & 1][ws][i];
+      }
+      if (tid == 0) s_piv[c] = prow;
+      T p = pr[k];
+      if (MODE == 3) {
+        // shifted pivot a_cc - s_c with s_c = -sign(a_cc): modulus >= 1
+        const T sgn = p >= T(0) ? T(-1) : T(1);
+        if (tid == 0) gmem<T>(d.sg)[k0 + c] = sgn;
+        p -= sgn;
+      } else if (p == T(0)) {
+        fail();
+        p = T(1);
+      }
+      ip[k] = T(1) / p;
+      const bool is_piv = tid == prow;
+      T z;
+      if (is_piv) pk = k;
+      if (MODE == 1) {
+        const bool upd = live && !used && !is_piv;
+        h[k] = upd ? -s[k] * ip[k] : T(0);
+        z = upd ? h[k] : s[k];
+        if (is_piv) {
+          used = true;
+          pc = c;
+        }
+      } else {
+        if (is_piv) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) s[i] *= ip[k];
+          z = ip[k];
+          used = true;
+        } else {
+          h[k] = -s[k] * ip[k];
+          z = h[k];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (i != k) s[i] = fma(h[k], pr[i], s[i]);
+      s[k] = z;
+      if (NOPIV) {
+        // the panel's later pivot rows, the same on every thread
+#pragma unroll
+        for (int j = k + 1; j < 4; ++j) {
+          const T hj = -G[j][k] * ip[k];
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (i != k) G[j][i] = fma(hj, pr[i], G[j][i]);
+          G[j][k] = hj;
+          hm[j][k] = hj;
+        }
       }
     }
+    if (!NOPIV) {
+      // the pivot rows as they were before the panel (their other slots are
+      // untouched so far), and what the panel's earlier steps do to them
+      if (pk >= 0) {
+        T *row = &prow_s[g][pk][0];
 #pragma unroll
-    for (int i = 0; i < BW; i += V) {
-      T pv[V];
-      *(uint4 *)pv = pr[i / V];
+        for (int i = 4; i < BW; ++i) row[i] = s[i];
 #pragma unroll
-      for (int v = 0; v < V; ++v)
-        if (i + v != k) s[i + v] = fma(h, pv[v], s[i + v]);
+        for (int j = 0; j < 4; ++j) hm_s[g][pk][j] = h[j];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 1; k < 4; ++k)
+#pragma unroll
+        for (int j = 0; j < k; ++j) hm[k][j] = c0 + k < wb ? hm_s[g][k][j] : T(0);
     }
-    s[k] = z;
+    uint64_t bk[4];          // waves with a pivot row scale it between its neighbours' updates
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bk[k] = MODE == 1 ? 0 : __ballot(pk == k);
+#pragma unroll
+    for (int q = 0; q < BW / 16; ++q) {
+      T pv[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) pv[k] = prow_s[g][k][16 * q + (lane & 15)];
+#pragma unroll
+      for (int k = 1; k < 4; ++k)
+#pragma unroll
+        for (int j = 0; j < k; ++j) pv[k] = fma(hm[k][j], pv[j], pv[k]);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (c0 + k >= wb) break;
+        if (q == 0) {
+          fmac4(s + 4, pv[k], h[k]);       // the first half row without the panel
+        } else {
+          fmac8<0>(s + 16 * q, pv[k], h[k]);
+        }
+        fmac8<8>(s + 16 * q + 8, pv[k], h[k]);
+        if (MODE != 1 && bk[k]) {
+          const T sc = pk == k ? ip[k] : T(1);
+#pragma unroll
+          for (int i = 16 * q; i < 16 * q + 16; ++i)
+            if (i >= 4) s[i] *= sc;
+        }
+      }
+    }
   };
   const int nsteps = (wb + 3) & ~3;
+#pragma unroll 1
   for (int c = 0; c < nsteps; c += 4) {
-    step(c, 0);
-    step(c + 1, 1);
-    step(c + 2, 2);
-    step(c + 3, 3);
+    panel(c);
     T t[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) t[i] = s[i];
@@ -1135,6 +1283,20 @@ __global__ __launch_bounds__(MAXT) void k_elim_block(const ElimDesc *__restrict_
     T *dst = A + (int64_t)tid * ld + k0;
     if (MODE == 1) {
       T *pb = gmem<T>(d.PB) + (int64_t)tid * BW;
+      if (vec) {               // whole block: slot i is column i
+#pragma unroll
+        for (int i = 0; i < BW; i += V) {
+          T a[V], y[V];
+#pragma unroll
+          for (int v = 0; v < V; ++v) {
+            const int col = i + v;
+            a[v] = pc == -2 || (pc >= 0 && col >= pc) ? s[col] : T(0);
+            y[v] = pc == -1 || (pc >= 0 && col < pc) ? s[col] : (col == pc ? T(1) : T(0));
+          }
+          *(uint4 *)(dst + i) = *(uint4 *)a;
+          *(uint4 *)(pb + i) = *(uint4 *)y;
+        }
+      } else {
 #pragma unroll
       for (int i = 0; i < BW; ++i) {
         const int col = (nsteps + i) & (BW - 1);
@@ -1156,6 +1318,7 @@ __global__ __launch_bounds__(MAXT) void k_elim_block(const ElimDesc *__restrict_
         }
         dst[col] = a;
         pb[col] = y;
+      }
       }
     } else if (vec) {
 #pragma unroll
