@@ -20,24 +20,76 @@
 namespace spand {
 
 // ------------------------------------------------------------------ utils
-template <typename T>
-__device__ inline T wave_sum(T v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+// v + (v of lane ^ O), every lane active.  The partner comes by lane moves in
+// the vector ALU (DPP within rows of 16, permlane swaps across them: 10-15
+// cycles) instead of a trip through the LDS crossbar (75 cycles a step, which
+// made a wave sum of doubles cost 510 cycles instead of 150).
+template <int O>
+__device__ inline double add_xor(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  if constexpr (O == 32 || O == 16) {
+    // the swap of a value with its copy leaves one row pair in each result
+    auto a = O == 32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                     : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    auto b = O == 32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                     : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __hiloint2double(int(b[0]), int(a[0])) + __hiloint2double(int(b[1]), int(a[1]));
+  } else {
+    int l, h;
+    if constexpr (O == 8) {           // row_ror:8
+      l = __builtin_amdgcn_update_dpp(0, lo, 0x128, 0xF, 0xF, false);
+      h = __builtin_amdgcn_update_dpp(0, hi, 0x128, 0xF, 0xF, false);
+    } else if constexpr (O == 4) {    // row_shl:4 into the even banks of 4, row_shr:4 into the odd ones
+      l = __builtin_amdgcn_update_dpp(0, lo, 0x104, 0xF, 0x5, false);
+      l = __builtin_amdgcn_update_dpp(l, lo, 0x114, 0xF, 0xA, false);
+      h = __builtin_amdgcn_update_dpp(0, hi, 0x104, 0xF, 0x5, false);
+      h = __builtin_amdgcn_update_dpp(h, hi, 0x114, 0xF, 0xA, false);
+    } else {                          // quad_perm
+      constexpr int C = O == 2 ? 0x4E : 0xB1;
+      l = __builtin_amdgcn_update_dpp(0, lo, C, 0xF, 0xF, false);
+      h = __builtin_amdgcn_update_dpp(0, hi, C, 0xF, 0xF, false);
+    }
+    return v + __hiloint2double(h, l);
+  }
+}
+__device__ inline double wave_sum(double v) {
+  v = add_xor<32>(v);
+  v = add_xor<16>(v);
+  v = add_xor<8>(v);
+  v = add_xor<4>(v);
+  v = add_xor<2>(v);
+  return add_xor<1>(v);
+}
+
+// Largest of v over each row of 16 lanes, in every lane of the row.
+__device__ inline uint32_t row16_max_u32(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, false));
   return v;
 }
 
-// block-wide sum of a double (blockDim multiple of 64, <= 1024)
-__device__ inline double block_sum(double v, double *red) {
+// Largest of v over the 64 lanes of a wave (every lane active), in every
+// lane: DPP max within each row of 16 (quad xor 1, quad xor 2, half-row
+// mirror, row mirror), then the four row results through readlane.
+__device__ inline uint32_t wave_max_u32(uint32_t v) {
+  v = row16_max_u32(v);
+  const uint32_t a = __builtin_amdgcn_readlane((int)v, 0), b = __builtin_amdgcn_readlane((int)v, 16);
+  const uint32_t c = __builtin_amdgcn_readlane((int)v, 32), d = __builtin_amdgcn_readlane((int)v, 48);
+  return max(max(a, b), max(c, d));
+}
+
+// Sum of a double over the first 256 threads of a workgroup.  red: 8 doubles;
+// par alternates between its halves from call to call, so that one barrier a
+// call is enough.
+__device__ inline double block_sum(double v, double *red, int &par) {
   v = wave_sum(v);
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  double *r = red + 4 * par;
+  par ^= 1;
+  if ((threadIdx.x & 63) == 0 && threadIdx.x < 256) r[threadIdx.x >> 6] = v;
   __syncthreads();
-  if (lane == 0) red[wid] = v;
-  __syncthreads();
-  double s = 0.0;
-  const int nw = blockDim.x >> 6;
-  for (int i = 0; i < nw; ++i) s += red[i];
-  return s;
+  return ((r[0] + r[1]) + r[2]) + r[3];
 }
 
 // ------------------------------------------------------------------ GEMM
@@ -880,26 +932,6 @@ int launch_elim_step(FType t, const ElimDesc *d_items, int nactive, int k, int m
   }
   SP_HIP(hipGetLastError());
   return SPAND_OK;
-}
-
-// Largest of v over the 64 lanes of a wave (every lane active), in every
-// lane: DPP max within each row of 16 (quad xor 1, quad xor 2, half-row
-// mirror, row mirror), then the four row results through readlane.
-__device__ inline uint32_t row16_max_u32(uint32_t v);
-__device__ inline uint32_t wave_max_u32(uint32_t v) {
-  v = row16_max_u32(v);
-  const uint32_t a = __builtin_amdgcn_readlane((int)v, 0), b = __builtin_amdgcn_readlane((int)v, 16);
-  const uint32_t c = __builtin_amdgcn_readlane((int)v, 32), d = __builtin_amdgcn_readlane((int)v, 48);
-  return max(max(a, b), max(c, d));
-}
-
-// Largest of v over each row of 16 lanes, in every lane of the row.
-__device__ inline uint32_t row16_max_u32(uint32_t v) {
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, false));
-  return v;
 }
 
 // Pivot key of a value: the bit pattern of |x| orders like |x| (NaN counts
@@ -1829,6 +1861,13 @@ __device__ inline void wg_gemm(int M, int N, int K, FA A, FB B, FE epi, double *
 //     from H alone.  A pivot outside the candidates ends the block.  The
 //     pivots are exactly those of the unblocked method; W is read once per
 //     block instead of once per step.
+//     Bound: from a few hundred rows on by the FP64 products of H (60% of the
+//     time at 224 x 3200), below that by the serial steps between them: sums
+//     and maxima over the workgroup, one barrier each (add_xor, block_sum with
+//     alternating halves, finish_argmax), and the projection on the stored
+//     q's, which reads 16 of them per round trip.  Before that (shuffles
+//     through LDS, two barriers a sum, one q at a time): 100 x 1000 alone 2.05
+//     ms, now 1.60; 77 x 333 1.81, now 1.32; 2048 of 224 x 3200 63.4, now 61.4.
 //  3. Completion to an orthogonal Q by Householder reconstruction (Ballard
 //     et al., "Reconstructing Householder vectors from tall-skinny QR",
 //     IPDPS 2014): with Q_c = [q_0 .. q_{k-1}] = [Q1; Q2] (Q1 k x k) and
@@ -1836,10 +1875,12 @@ __device__ inline void wg_gemm(int M, int N, int K, FA A, FB B, FE epi, double *
 //     H = I + (Q_c S - E) [I, G2^T] with G2 = Q2 (Q1 - S)^-1, E = [I_k; 0],
 //     is orthogonal and H E = Q_c S.  Output Q = [Q_c | H(:, k:m)].
 //     Rows k.. of V receive G2 S; tau receives S.
-template <typename T, int BQ>
-__global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ items, double eps,
+template <typename T, int BQ, int NT>
+__global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_qrcp(const QrcpDesc *__restrict__ items, double eps,
                                               int force_full, int MS, int GS, int complete) {
   static_assert(BQ % 2 == 0, "H is read in pairs");
+  static_assert(NT == 256 || NT == 512, "sums over rows are laid out for 256 threads");
+  constexpr int NW = NT / 64;
   const QrcpDesc d = items[blockIdx.x];
   const int m = d.m, nc = d.ncols;
   const int64_t ldw = d.ldw;
@@ -1864,19 +1905,22 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
   int *act = reinterpret_cast<int *>(av + BQ);
   int *sidx = act + GS;
   double *H = gmem<double>(d.H);                  // ldw x BQ: column j of B W at H + j BQ
-  __shared__ int s_j, s_nflag, s_nf, s_in;
-  __shared__ double rv[4];
-  __shared__ int ri[4];
+  __shared__ int s_nflag, s_nf;
+  __shared__ __align__(16) uint64_t rk_s[2][NW];   // pivot search: a wave's best norm (bits) and column
+  __shared__ __align__(16) int ri_s[2][NW];
+  int rpar = 0, bpar = 0;             // halves of rk_s / red in use
   __shared__ double cnw[BQ];
-  __shared__ int wtot[4];
+  __shared__ int wtot[NW];
   __shared__ int s_fl[64];
-  __shared__ double red[16];
+  __shared__ double red[8];
+  __shared__ double cmx[NW];
+  __shared__ double n0_s[4][BQ];
   __shared__ double s_piv;
   const double tol3z = 1.4901161193847656e-08;  // sqrt(2^-52)
 
   // c[t] = q_t . x for t < n (one wave per 4 consecutive t)
   auto qdots = [&](const double *x, int n, double *c) {
-    for (int t0 = wid * 4; t0 < n; t0 += 16) {
+    for (int t0 = wid * 4; t0 < n; t0 += 4 * NW) {
       const T *q0 = Qt + (int64_t)t0 * m;
       double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
 #pragma unroll 4
@@ -1902,7 +1946,7 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
   };
   // x -= sum_{t<n} c[t] q_t (eight independent sums keep eight loads in flight)
   auto qsub = [&](double *x, int n, const double *c) {
-    for (int r = tid; r < m; r += 256) {
+    for (int r = tid; r < m; r += NT) {
       double sv[8];
 #pragma unroll
       for (int q = 0; q < 8; ++q) sv[q] = 0.0;
@@ -1919,7 +1963,7 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
   };
 
   // ---- 1. column norms, VN adjacent columns per thread with 16-byte loads
-  for (int g = tid; g < ngrp; g += 256) {
+  for (int g = tid; g < ngrp; g += NT) {
     double acc[VN];
 #pragma unroll
     for (int q = 0; q < VN; ++q) acc[q] = 0.0;
@@ -1952,12 +1996,14 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
   }
   __syncthreads();
   double cmax = 0.0;
-  for (int j = tid; j < nc; j += 256) cmax = fmax(cmax, vn1[j]);
+  for (int j = tid; j < nc; j += NT) cmax = fmax(cmax, vn1[j]);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) cmax = fmax(cmax, __shfl_xor(cmax, o, 64));
-  if (lane == 0) red[wid] = cmax;
+  if (lane == 0) cmx[wid] = cmax;
   __syncthreads();
-  cmax = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  cmax = cmx[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) cmax = fmax(cmax, cmx[w]);
   // |R_00| is the largest column norm; the 1e-4 margin keeps a column whose
   // norm ties the threshold up to rounding
   const double thr = force_full ? 0.0 : eps * cmax * (1.0 - 1e-4);
@@ -1990,7 +2036,7 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
   // only written at or below the position they are read from.
   auto filter = [&](const int *src, int n, int *dst) {
     int base = 0;
-    for (int q0 = 0; q0 < n; q0 += 256) {
+    for (int q0 = 0; q0 < n; q0 += NT) {
       const int qa = q0 + tid;
       const int g = qa < n ? (src ? src[qa] : qa) : 0;
       const bool keep = qa < n && live_group(g);
@@ -2000,7 +2046,7 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
       int off = base;
       for (int w = 0; w < wid; ++w) off += wtot[w];
       if (keep) dst[off + __popcll(bal & ((1ull << lane) - 1ull))] = g;
-      base += wtot[0] + wtot[1] + wtot[2] + wtot[3];
+      for (int w = 0; w < NW; ++w) base += wtot[w];
       __syncthreads();
     }
     return base;
@@ -2025,34 +2071,54 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
   // largest vn1 over the unselected columns of the live groups, ties ->
   // smallest index (the packed layouts keep the column order)
   int ncand_in = 0;               // candidates the pivot search checks against
-  // block-wide maximum of the threads' (value, index) pairs: s_j, and s_in
-  // = whether it is one of the block's candidates
+  // block-wide maximum of the threads' (value, index) pairs (value -1: none),
+  // ties -> smallest index, INT_MAX if there is none; s_in = whether it is one
+  // of the block's candidates.  Norms are not negative, so their bits order
+  // like they do.  Waves meet in LDS (one barrier, alternating buffers), every
+  // thread takes the best of them itself.
+  bool s_in = false;
   auto finish_argmax = [&](double bv, int bi) {
+    const bool ok = bv >= 0.0;
+    const uint64_t key = ok ? uint64_t(__double_as_longlong(bv)) : 0;
+    const uint32_t hi = uint32_t(key >> 32), lo = uint32_t(key);
+    const uint32_t mh = wave_max_u32(hi);
+    const bool c1 = ok && hi == mh;
+    const uint32_t ml = wave_max_u32(c1 ? lo : 0u);
+    const bool c2 = c1 && lo == ml;
+    const uint64_t b = __ballot(c2);
+    int wi = INT_MAX;
+    if (b) {
+      if (b & (b - 1)) wi = int(~wave_max_u32(c2 ? ~uint32_t(bi) : 0u));
+      else wi = __builtin_amdgcn_readlane(bi, int(__builtin_ctzll(b)));
+    }
+    uint64_t *rk = rk_s[rpar];
+    int *ri = ri_s[rpar];
+    rpar ^= 1;
+    if (lane == 0) {
+      rk[wid] = (uint64_t(mh) << 32) | ml;
+      ri[wid] = wi;
+    }
+    __syncthreads();
+    const int cs = lane < ncand_in ? sidx[lane] : -1;
+    uint64_t v = rk[0];
+    int ii = ri[0];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const double ov = __shfl_xor(bv, o, 64);
-      const int oi = __shfl_xor(bi, o, 64);
-      if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+    for (int q = 1; q < NW; ++q) {
+      const uint64_t vq = rk[q];
+      const int iq = ri[q];
+      if (iq != INT_MAX && (ii == INT_MAX || vq > v || (vq == v && iq < ii))) {
+        v = vq;
+        ii = iq;
+      }
     }
-    if (lane == 0) { rv[wid] = bv; ri[wid] = bi; }
-    __syncthreads();
-    if (tid == 0) {
-      double v = rv[0];
-      int ii = ri[0];
-      for (int q = 1; q < 4; ++q)
-        if (rv[q] > v || (rv[q] == v && ri[q] < ii)) { v = rv[q]; ii = ri[q]; }
-      s_j = ii;
-      int f = 0;                  // is it one of the block's candidates?
-      for (int cq = 0; cq < ncand_in; ++cq) f |= sidx[cq] == ii;
-      s_in = f;
-    }
-    __syncthreads();
-    return s_j;
+    ii = __builtin_amdgcn_readfirstlane(ii);
+    s_in = __ballot(cs == ii) != 0;
+    return ii;
   };
   auto argmax_col = [&](int nact) {
     double bv = -1.0;
     int bi = INT_MAX;
-    for (int qa = tid; qa < nact; qa += 256) {
+    for (int qa = tid; qa < nact; qa += NT) {
       const int g = act[qa];
       int sg[VN];
       double vg[VN];
@@ -2069,7 +2135,7 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
   };
   // c[l] = b_l . x and x -= sum_l c[l] b_l for the basis rows of Bm
   auto bdots = [&](const double *x, int n, double *c) {
-    for (int l = wid; l < n; l += 4) {
+    for (int l = wid; l < n; l += NW) {
       double a = 0.0;
       for (int r = lane; r < m; r += 64) a += Bm[l * MS + r] * x[r];
       a = wave_sum(a);
@@ -2077,13 +2143,15 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
     }
     __syncthreads();
   };
-  auto bsub = [&](double *x, int n, const double *c) {
-    for (int r = tid; r < m; r += 256) {
+  // Sums over rows go by the first 256 threads (row r: thread r mod 256), and
+  // so does what is done to the rows between them.
+  const int row0 = tid < 256 ? tid : m;
+  auto bsub = [&](double *x, int n, const double *c) {   // each thread its own rows
+    for (int r = row0; r < m; r += 256) {
       double sv = 0.0;
       for (int l = 0; l < n; ++l) sv += Bm[l * MS + r] * c[l];
       x[r] -= sv;
     }
-    __syncthreads();
   };
   bool done = false;
   while (!done && k < imax) {
@@ -2100,13 +2168,13 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
     if (2 * nact_cur <= cur_ngrp) {
       const int na = nact_cur;
       T *dst = Wother;
-      for (int r = wid; r < m; r += 4)
+      for (int r = wid; r < m; r += NW)
         for (int p = lane; p < na; p += 64)
           *reinterpret_cast<VT *>(dst + (int64_t)r * ldw + p * VN) =
               *reinterpret_cast<const VT *>(W + (int64_t)r * ldw + act[p] * VN);
       // norms and flags, in rounds: a source position is never below its
       // destination, so reading a round completely before writing it is safe
-      for (int p0 = 0; p0 < na * VN; p0 += 256) {
+      for (int p0 = 0; p0 < na * VN; p0 += NT) {
         const int pos = p0 + tid;
         double a1 = 0.0, a2 = 0.0;
         int sf = 1;
@@ -2124,7 +2192,7 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
         }
         __syncthreads();
       }
-      for (int p = tid; p < na; p += 256) act[p] = p;
+      for (int p = tid; p < na; p += NT) act[p] = p;
       Wother = const_cast<T *>(W);
       W = dst;
       cur_ngrp = na;
@@ -2142,7 +2210,7 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
 #pragma unroll
       for (int c = 0; c < BQ; ++c) { tv[c] = -1.0; ti[c] = INT_MAX; }
       auto better = [](double v, int j, double w, int i) { return v > w || (v == w && j < i); };
-      for (int qa = tid; qa < nact_cur; qa += 256) {
+      for (int qa = tid; qa < nact_cur; qa += NT) {
         const int g = act[qa];
 #pragma unroll 1
         for (int q = 0; q < VN; ++q) {
@@ -2189,13 +2257,13 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
     // candidates that do not enter are dropped from the block (compacted
     // out of sidx): if one of them becomes the pivot, the block ends and
     // the next one starts with it.
-    for (int e = tid; e < ncand * m; e += 256) {
+    for (int e = tid; e < ncand * m; e += NT) {
       const int cq = e / m, r = e - cq * m;
       Bm[cq * MS + r] = double(W[(int64_t)r * ldw + sidx[cq]]);
     }
-    for (int e = ncand * MS + tid; e < BQ * MS; e += 256) Bm[e] = 0.0;
+    for (int e = ncand * MS + tid; e < BQ * MS; e += NT) Bm[e] = 0.0;
     __syncthreads();
-    for (int cq = wid; cq < ncand; cq += 4) {
+    for (int cq = wid; cq < ncand; cq += NW) {
       double a2 = 0.0;
       for (int r = lane; r < m; r += 64) a2 += Bm[cq * MS + r] * Bm[cq * MS + r];
       a2 = wave_sum(a2);
@@ -2208,7 +2276,7 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
     for (int pass = 0; pass < 2 && k > 0; ++pass) {
       {
         const int tl = lane & 15, rq = lane >> 4;
-        for (int t0 = wid * 16; t0 < k; t0 += 64) {
+        for (int t0 = wid * 16; t0 < k; t0 += 16 * NW) {
           const int t = t0 + tl;
           double a[BQ];
 #pragma unroll
@@ -2237,8 +2305,8 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
           }
 #pragma unroll
           for (int cq = 0; cq < BQ; ++cq) {
-            a[cq] += __shfl_xor(a[cq], 16, 64);
-            a[cq] += __shfl_xor(a[cq], 32, 64);
+            a[cq] = add_xor<16>(a[cq]);
+            a[cq] = add_xor<32>(a[cq]);
           }
           if (rq == 0 && t < k)
 #pragma unroll
@@ -2246,49 +2314,82 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
         }
       }
       __syncthreads();
-      for (int r = tid; r < m; r += 256) {
-        double sv[BQ];
+      // U -= Q_k P: a thread takes CS candidates of a row (a part of them where
+      // several sets of threads cover the rows), 16 rows' loads per round trip,
+      // products in order of t
+      auto psub = [&](auto csc, int r, int c0) {
+        constexpr int CS = decltype(csc)::value;
+        double sv[CS];
 #pragma unroll
-        for (int cq = 0; cq < BQ; ++cq) sv[cq] = 0.0;
+        for (int c = 0; c < CS; ++c) sv[c] = 0.0;
+        auto add = [&](T q, int t) {
+#pragma unroll
+          for (int c = 0; c < CS; ++c) sv[c] += P[t * BQ + c0 + c] * double(q);
+        };
         int t = 0;
-        for (; t + 8 <= k; t += 8) {       // eight loads per round trip, products in order
-          T qv[8];
+        for (; t + 16 <= k; t += 16) {
+          T qv[16];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) qv[u] = Qt[(int64_t)(t + u) * m + r];
+          for (int u = 0; u < 16; ++u) qv[u] = Qt[(int64_t)(t + u) * m + r];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) asm volatile("" ::"v"(qv[u]));
+          for (int u = 0; u < 16; ++u) asm volatile("" ::"v"(qv[u]));
 #pragma unroll
-          for (int u = 0; u < 8; ++u)
-#pragma unroll
-            for (int cq = 0; cq < BQ; ++cq) sv[cq] += P[(t + u) * BQ + cq] * double(qv[u]);
+          for (int u = 0; u < 16; ++u) add(qv[u], t + u);
         }
-        for (; t < k; ++t) {
-          const double qv = double(Qt[(int64_t)t * m + r]);
+        if (t < k) {                       // the rest: past the end the last row again, not used
+          T qv[16];
 #pragma unroll
-          for (int cq = 0; cq < BQ; ++cq) sv[cq] += P[t * BQ + cq] * qv;
+          for (int u = 0; u < 16; ++u) qv[u] = Qt[(int64_t)min(t + u, k - 1) * m + r];
+#pragma unroll
+          for (int u = 0; u < 16; ++u) asm volatile("" ::"v"(qv[u]));
+#pragma unroll
+          for (int u = 0; u < 16; ++u)
+            if (t + u < k) add(qv[u], t + u);
         }
 #pragma unroll
-        for (int cq = 0; cq < BQ; ++cq) Bm[cq * MS + r] -= sv[cq];
+        for (int c = 0; c < CS; ++c) Bm[(c0 + c) * MS + r] -= sv[c];
+      };
+      constexpr int S1 = NT / 128, S2 = NT / 256;   // sets over 128 and 256 rows
+      if (BQ >= S1 && m <= 128) {
+        const int r = tid & 127;
+        if (r < m) psub(std::integral_constant<int, (BQ >= S1 ? BQ / S1 : BQ)>{}, r, (tid >> 7) * (BQ / S1));
+      } else {
+        for (int r = tid & 255; r < m; r += 256)
+          psub(std::integral_constant<int, BQ / S2>{}, r, (tid >> 8) * (BQ / S2));
+      }
+      __syncthreads();
+    }
+    // residual norms of all candidates at once (one barrier)
+    {
+      double s0[BQ];
+#pragma unroll
+      for (int cq = 0; cq < BQ; ++cq) s0[cq] = 0.0;
+      for (int r = row0; r < m; r += 256)
+#pragma unroll
+        for (int cq = 0; cq < BQ; ++cq) s0[cq] += Bm[cq * MS + r] * Bm[cq * MS + r];
+#pragma unroll
+      for (int cq = 0; cq < BQ; ++cq) {
+        s0[cq] = wave_sum(s0[cq]);
+        if (lane == 0 && wid < 4) n0_s[wid][cq] = s0[cq];
       }
       __syncthreads();
     }
     int nb = 0;
     for (int cq = 0; cq < ncand; ++cq) {
       double *x = Bm + cq * MS;
-      double s0 = 0.0;
-      for (int r = tid; r < m; r += 256) s0 += x[r] * x[r];
-      const double n0 = sqrt(block_sum(s0, red));
+      const double n0 = sqrt(((n0_s[0][cq] + n0_s[1][cq]) + n0_s[2][cq]) + n0_s[3][cq]);
       for (int pass = 0; pass < 2 && nb > 0; ++pass) {
+        if (pass) __syncthreads();
         bdots(x, nb, cbuf);
         bsub(x, nb, cbuf);
       }
       double s1 = 0.0;
-      for (int r = tid; r < m; r += 256) s1 += x[r] * x[r];
-      const double n1 = sqrt(block_sum(s1, red));
+      for (int r = row0; r < m; r += 256) s1 += x[r] * x[r];
+      const double n1 = sqrt(block_sum(s1, red, bpar));
       if (n1 > 0.0 && (cq == 0 || (n1 > 1e-2 * n0 && n0 > 1e-4 * cnw[cq]))) {
         const double inv = 1.0 / n1;
         // row cq moves to row nb <= cq (each thread moves its own entries)
-        for (int r = tid; r < m; r += 256) Bm[nb * MS + r] = x[r] * inv;
+        for (int r = row0; r < m; r += 256) Bm[nb * MS + r] = x[r] * inv;
         if (tid == 0) sidx[nb] = sidx[cq];
         ++nb;
       }
@@ -2298,15 +2399,16 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
     ncand_in = nb;
     // the next pivot itself has no residual left: the unblocked method stops there
     if (nb == 0) break;
-    for (int e = nb * MS + tid; e < BQ * MS; e += 256) Bm[e] = 0.0;
+    for (int e = nb * MS + tid; e < BQ * MS; e += NT) Bm[e] = 0.0;
     __syncthreads();
     // (c) H = Bm W for the live columns: one pass over W.  With few active
     // groups, RS adjacent lanes split the rows of one group (in blocks of 4)
-    // and combine their sums by shuffles.
+    // and combine their sums by lane moves (RS by the groups alone, so that the
+    // sums do not depend on NT).
     {
       int RS = 1;
       while (RS < 8 && nact_cur * RS * 2 <= 256) RS *= 2;
-      const int sl = tid % RS, ga = tid / RS, gpp = 256 / RS;
+      const int sl = tid % RS, ga = tid / RS, gpp = NT / RS;
       const int m4 = m & ~3;
       for (int qa0 = 0; qa0 < nact_cur; qa0 += gpp) {
         const int qa = qa0 + ga;
@@ -2346,11 +2448,14 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
               }
             }
         }
-        for (int o = 1; o < RS; o <<= 1)
 #pragma unroll
-          for (int q = 0; q < VN; ++q)
+        for (int q = 0; q < VN; ++q)
 #pragma unroll
-            for (int l = 0; l < BQ; ++l) acc[q][l] += __shfl_xor(acc[q][l], o, 64);
+          for (int l = 0; l < BQ; ++l) {
+            if (RS > 1) acc[q][l] = add_xor<1>(acc[q][l]);
+            if (RS > 2) acc[q][l] = add_xor<2>(acc[q][l]);
+            if (RS > 4) acc[q][l] = add_xor<4>(acc[q][l]);
+          }
         if (live && sl == 0) {
           double *hg = H + (int64_t)g * VN * BQ;
 #pragma unroll
@@ -2382,12 +2487,15 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
         double v = H[(int64_t)js * BQ + l];
         for (int pass = 0; pass < 2 && nst > 0; ++pass) {
           const double ct = t < nst ? Cc[t * BQ + l] : 0.0;
-          double dt = ct * v;
-#pragma unroll
-          for (int o = 1; o < BQ; o <<= 1) dt += __shfl_xor(dt, o, 64);
+          double dt = add_xor<1>(ct * v);
+          if (BQ > 2) dt = add_xor<2>(dt);
+          if (BQ > 4) dt = add_xor<4>(dt);
           double w = dt * ct;
-#pragma unroll
-          for (int o = BQ; o < 64; o <<= 1) w += __shfl_xor(w, o, 64);
+          if (BQ <= 2) w = add_xor<2>(w);
+          if (BQ <= 4) w = add_xor<4>(w);
+          w = add_xor<8>(w);
+          w = add_xor<16>(w);
+          w = add_xor<32>(w);
           v -= w;
         }
         const double nrm = sqrt(wave_sum(lane < BQ ? v * v : 0.0));
@@ -2400,7 +2508,7 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
       // below the floor the residual is rounding noise and Gram-Schmidt
       // could no longer make it orthogonal: the completion supplies the rest
       if (nrm == 0.0 || nrm <= stop_rel * R00) { done = true; break; }
-      for (int r = tid; r < m; r += 256) {
+      for (int r = tid; r < m; r += NT) {
         double sv = 0.0;
 #pragma unroll
         for (int l = 0; l < BQ; ++l) sv += Bm[l * MS + r] * ck[l];
@@ -2445,7 +2553,7 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
         }
         if (v > nbv || (v == nbv && j < nbi)) { nbv = v; nbi = j; }
       };
-      for (int qa = tid; qa < nact_cur; qa += 256) {
+      for (int qa = tid; qa < nact_cur; qa += NT) {
         const int g = act[qa];
         const double *hg = H + (int64_t)g * VN * BQ;
 #pragma unroll
@@ -2475,13 +2583,14 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
       __syncthreads();
       // without recomputed norms the search is complete; otherwise it is
       // repeated after the recomputation
-      js_next = s_nflag > 0 ? -1 : finish_argmax(nbv, nbi);
-      if (s_nflag > 0) {
+      const bool again = s_nflag > 0;
+      js_next = again ? -1 : finish_argmax(nbv, nbi);
+      if (again) {
         // exact residual norms of the flagged columns against q_0..q_k
         for (;;) {
           if (tid == 0) s_nf = 0;
           __syncthreads();
-          for (int qa = tid; qa < nact_cur; qa += 256) {
+          for (int qa = tid; qa < nact_cur; qa += NT) {
             const int g = act[qa];
 #pragma unroll
             for (int q = 0; q < VN; ++q) {
@@ -2497,13 +2606,13 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
           if (nf == 0) break;
           for (int f = 0; f < nf; ++f) {
             const int j = s_fl[f];
-            for (int r = tid; r < m; r += 256) u[r] = double(W[(int64_t)r * ldw + j]);
+            for (int r = tid; r < m; r += NT) u[r] = double(W[(int64_t)r * ldw + j]);
             __syncthreads();
             qdots(u, k + 1, cbuf);
             qsub(u, k + 1, cbuf);
             double s2 = 0.0;
-            for (int r = tid; r < m; r += 256) s2 += u[r] * u[r];
-            s2 = block_sum(s2, red);
+            for (int r = row0; r < m; r += 256) s2 += u[r] * u[r];
+            s2 = block_sum(s2, red, bpar);
             if (tid == 0) {
               vn1[j] = sqrt(s2);
               vn2[j] = vn1[j];
@@ -2521,6 +2630,7 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
   // ---- 3. complete Q (unless the caller completes it in batched launches
   // from the k_gs kept vectors)
   if (tid == 0) *d.k_gs = k;
+  if constexpr (NT == 256) {        // the completion is laid out for 256 threads
   double *As = qsm, *Bs = qsm + 1024;
   if (complete && k == 0) {
     for (int i2 = tid >> 4; i2 < m; i2 += 16)
@@ -2580,6 +2690,7 @@ __global__ __launch_bounds__(256, 3) void k_qrcp(const QrcpDesc *__restrict__ it
     for (int r = tid >> 4; r < m; r += 16)
       for (int t = tid & 15; t < k; t += 16) Q[(int64_t)r * m + t] = Qt[(int64_t)t * m + r];
   }
+  }
   if (tid == 0) *d.k_out = force_full ? m : k;
 }
 
@@ -2605,21 +2716,33 @@ int launch_qrcp(FType t, const QrcpDesc *d_items, int n, double eps, int force_f
     set_error("RRQR launch: block width %d, %zu bytes of LDS", bq, lds);
     return SPAND_EINVAL;
   }
+  // One interface is one workgroup's work.  A launch of at most one interface
+  // per compute unit (256; the upper levels) takes 512 threads where an
+  // interface has more than 128 rows: two waves per SIMD hide the loads'
+  // latency (FP32, 224 x 3200: 11.8 -> 9.2 ms at 256 interfaces; FP64, 200 x
+  // 2000: 9.0 -> 6.3 ms at 128).  More interfaces fill the units with
+  // workgroups of 256 (16.9 against 18.3 ms at 512 of 224 x 3200), and up to
+  // 128 rows the longer barriers cost what the loads gain (100 x 1000: 1.86
+  // against 1.87 ms).  Every sum is taken in the same order at both widths.
+  const bool wide = n <= 256 && MS > 128 && !complete;
+#define QRCP_LAUNCH(T, B, NT)                                                                   \
+  hipLaunchKernelGGL((k_qrcp<T, B, NT>), dim3(n), dim3(NT), lds, st, d_items, eps, force_full, MS, GS, complete)
+#define QRCP_WIDTH(T, B)                                                                        \
+  do {                                                                                          \
+    if (wide) QRCP_LAUNCH(T, B, 512);                                                           \
+    else QRCP_LAUNCH(T, B, 256);                                                                \
+  } while (0)
   if (t == FType::F64) {
-    if (bq == 8)
-      hipLaunchKernelGGL((k_qrcp<double, 8>), dim3(n), dim3(256), lds, st, d_items, eps, force_full, MS, GS, complete);
-    else if (bq == 4)
-      hipLaunchKernelGGL((k_qrcp<double, 4>), dim3(n), dim3(256), lds, st, d_items, eps, force_full, MS, GS, complete);
-    else
-      hipLaunchKernelGGL((k_qrcp<double, 2>), dim3(n), dim3(256), lds, st, d_items, eps, force_full, MS, GS, complete);
+    if (bq == 8) QRCP_WIDTH(double, 8);
+    else if (bq == 4) QRCP_WIDTH(double, 4);
+    else QRCP_WIDTH(double, 2);
   } else {
-    if (bq == 8)
-      hipLaunchKernelGGL((k_qrcp<float, 8>), dim3(n), dim3(256), lds, st, d_items, eps, force_full, MS, GS, complete);
-    else if (bq == 4)
-      hipLaunchKernelGGL((k_qrcp<float, 4>), dim3(n), dim3(256), lds, st, d_items, eps, force_full, MS, GS, complete);
-    else
-      hipLaunchKernelGGL((k_qrcp<float, 2>), dim3(n), dim3(256), lds, st, d_items, eps, force_full, MS, GS, complete);
+    if (bq == 8) QRCP_WIDTH(float, 8);
+    else if (bq == 4) QRCP_WIDTH(float, 4);
+    else QRCP_WIDTH(float, 2);
   }
+#undef QRCP_WIDTH
+#undef QRCP_LAUNCH
   SP_HIP(hipGetLastError());
   return SPAND_OK;
 }
