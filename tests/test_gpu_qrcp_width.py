@@ -14,7 +14,7 @@ from synth.dg_euler import DGConfig, make_problem  # noqa: E402
 
 
 @pytest.mark.parametrize("n,p,L,nsys,dtype,eps", [
-    (24, 3, 6, 8, "f32", 1e-2),    # interfaces of 3 elements of 40 and of 6: 120 and 240 rows
+    (24, 3, 6, 8, "f32", 1e-2),    # 64 unknowns an element: 192 and 384 rows
     (24, 3, 6, 8, "f64", 1e-3),
     (33, 2, 7, 6, "f32", 1e-1),    # odd counts
     (33, 2, 6, 12, "f64", 1e-2),
