@@ -85,6 +85,7 @@ static float time_median(hipStream_t st, F &&fn) {
 }
 
 int autotune_spmv(const spand_bsr_t &A, double *x, double *y, hipStream_t st) {
+  if (spmv_by_wave(A)) return SPAND_OK;          // no lane groups to tune
   std::lock_guard<std::mutex> lk(g_tune_mu);
   load_cache_locked();
   if (g_spmv.count(A.bs)) return SPAND_OK;

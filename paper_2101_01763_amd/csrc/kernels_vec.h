@@ -15,6 +15,8 @@ constexpr int GEMV_TROWS = 64;    // output rows of a transposed GEMV band
 int launch_pull2(FType t, const PullGroup *d_groups, const PullItem *d_items,
                  const PullChunk *d_chunks, int nchunks, int trans, const double *in,
                  const double *base, double *out, double alpha, hipStream_t st);
+// whether the product y = A x takes one wave per element instead of tuned lane groups
+bool spmv_by_wave(const spand_bsr_t &A);
 int launch_spmv_g(const spand_bsr_t &A, int G, double alpha, const double *x, double beta,
                   double *y, const double *z, double gz, const double *w, double gw,
                   hipStream_t st);

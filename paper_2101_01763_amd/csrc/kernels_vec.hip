@@ -529,6 +529,92 @@ __global__ __launch_bounds__(256) void k_spmv(int n_brows, int bs, const int32_t
   }
 }
 
+// The same product with one wave per element, for the block sizes
+// 4 (p + 1)^2 of p = 1 and 2: L = BS / 2 lanes
+// cover a block row and S = 64 / L slices of lanes take every S-th row, so an
+// instruction reads up to 1 KB of the element's contiguous blocks and a block's
+// part of x is read once, not once per row.  A lane keeps the partial sums of
+// its K = BS / S rows; LDS adds the L lanes of a row at the end.  U blocks
+// of a row are in flight per wave (a cell's five of BS = 16).
+// Bound by the one read of the values: 1.9 GB of BS = 36 in 295 us (6.5 TB/s;
+// k_spmv 455 us), 2.7 GB of BS = 16 in 424 us (590 us).
+template <int BS>
+struct SpmvWave {
+  static constexpr int L = BS / 2, S = 64 / L, K = BS / S, P = L + 1 - (L & 1);
+  static constexpr int U = K < 10 ? 10 / K : 1;
+  static_assert(K * S == BS, "slices cover the rows evenly");
+};
+template <int BS>
+__global__ __launch_bounds__(256) void k_spmv_wave(int n_brows, const int32_t *__restrict__ rowptr,
+                                                   const int32_t *__restrict__ colind,
+                                                   const double *__restrict__ val,
+                                                   const double *__restrict__ x, double alpha,
+                                                   double beta, double *__restrict__ y,
+                                                   const double *__restrict__ z, double gz,
+                                                   const double *__restrict__ w, double gw) {
+  using W = SpmvWave<BS>;
+  constexpr int L = W::L, S = W::S, K = W::K, P = W::P, U = W::U;
+  __shared__ double part[4][BS * P];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int I = blockIdx.x * 4 + wv;
+  if (I >= n_brows) return;                // whole waves; each uses its own part of LDS
+  const int lane = threadIdx.x & 63;
+  const int sl = min(lane / L, S - 1), i = lane % L;      // lanes past S L repeat the last slice's loads
+  spmv_f64x2 a[K] = {};
+  const int t1 = rowptr[I + 1];
+  const int t0 = rowptr[I];
+  int J[U];                                // one round ahead of the loads that need it
+  auto cols = [&](int t) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) J[u] = colind[min(t + u, t1 - 1)];
+  };
+  if (t0 < t1) cols(t0);
+  for (int t = t0; t < t1; t += U) {
+    spmv_f64x2 xv[U], e[U][K];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const double *blk = val + (int64_t)min(t + u, t1 - 1) * (BS * BS) + sl * BS + 2 * i;
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        e[u][k] = __builtin_nontemporal_load(reinterpret_cast<const spmv_f64x2 *>(blk + k * S * BS));
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const double *xp = x + (int64_t)J[u] * BS + 2 * i;
+      xv[u] = spmv_f64x2{xp[0], xp[1]};
+    }
+    cols(t + U);
+    // every load is issued before the first product (left to itself the
+    // compiler moves each to its use, one wait per load)
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < K; ++k) asm volatile("" : "+v"(e[u][k]));
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (t + u < t1)
+#pragma unroll
+        for (int k = 0; k < K; ++k) a[k] += e[u][k] * xv[u];
+  }
+  if (lane < L * S)
+#pragma unroll
+    for (int k = 0; k < K; ++k) part[wv][(sl + k * S) * P + i] = a[k][0] + a[k][1];
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  if (lane < BS) {
+    const double *pr = part[wv] + lane * P;
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int q = 0; q < L; q += 2) s0 += pr[q], s1 += q + 1 < L ? pr[q + 1] : 0.0;
+    const int64_t R = (int64_t)I * BS + lane;
+    double v = alpha * (s0 + s1);
+    if (beta != 0.0) v += beta * y[R];
+    if (z) v += gz * z[R];
+    if (w) v += gw * w[R];
+    y[R] = v;
+  }
+}
+
 static int g_spmv_lanes[65] = {0};   // per block size; 0 = not tuned (default 8)
 
 void set_spmv_lanes(int bs, int G) {
@@ -715,9 +801,24 @@ int launch_spmv_t_check(const spand_bsr_t &A, int *d_flag, hipStream_t st) {
   return SPAND_OK;
 }
 
+bool spmv_by_wave(const spand_bsr_t &A) {
+  return (A.bs == 16 || A.bs == 36) && (reinterpret_cast<uintptr_t>(A.d_val) & 15) == 0;
+}
+
 int launch_spmv(const spand_bsr_t &A, int transpose, double alpha, const double *x, double beta,
                 double *y, const double *z, double gz, const double *w, double gw,
                 hipStream_t st) {
+  // One wave per element beats the lane groups at bs = 16 and 36 at every size
+  // (256 elements of 36: 10.1 against 11.5 us a call); at 64 a group of 8 reads a row's 512 bytes evenly and is faster
+  // (10.7 GB: 1.53 ms against 1.65 ms for 32 rows' sums per lane).
+  if (!transpose && spmv_by_wave(A)) {
+    if (A.n_brows <= 0) return SPAND_OK;
+    auto *k = A.bs == 16 ? k_spmv_wave<16> : k_spmv_wave<36>;
+    hipLaunchKernelGGL(k, dim3((unsigned)cdiv(A.n_brows, 4)), dim3(256), 0, st, A.n_brows, A.d_rowptr, A.d_colind,
+                       A.d_val, x, alpha, beta, y, z, gz, w, gw);
+    SP_HIP(hipGetLastError());
+    return SPAND_OK;
+  }
   if (!transpose) return launch_spmv_g(A, get_spmv_lanes(A.bs), alpha, x, beta, y, z, gz, w, gw, st);
   const int64_t N = (int64_t)A.n_brows * A.bs;
   if (N == 0) return SPAND_OK;
