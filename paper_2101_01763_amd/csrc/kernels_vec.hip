@@ -6,6 +6,7 @@
 
 #include "internal.h"
 #include "kernels_vec.h"
+#include "lanes.h"
 
 namespace spand {
 
@@ -25,6 +26,10 @@ __device__ inline T wsum(T v) {
 // backward sweep's A_ss^-1 (x_s + c) is t + A_ss^-1 c on those rows, a product
 // with nb columns.  So n^2 + nb^2 elements are read instead of 2 n^2 (measured
 // at Factor::sweeps).
+// Four rows' sums used to be shuffled through LDS and their slots loaded after
+// them, with no load of the matrix in flight: 4.5 TB/s on matrices of ~220
+// columns, now 5.6 (374 -> 292 us for 8128 of them), and 6.05 TB/s on leaves of
+// ~580 (841 + 903 -> 811 + 825 us for 4096, FP32).
 // One workgroup per band of output rows (GemvChunk).  The input is staged
 // in LDS.  Bands of one item may run concurrently, so in == out is not
 // allowed (the sweeps alternate between two vectors).
@@ -64,56 +69,83 @@ __global__ __launch_bounds__(256) void k_gemv(const GemvDesc *__restrict__ items
   __shared__ double part[256];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   if (ch.kind == GEMV_EDGE) d.cols = d.nb;
-  for (int c = tid; c < d.cols; c += 256) {
-    const int s = gmem<const int32_t>(d.islot)[c];
-    double v = ch.kind == GEMV_EDGE ? corr[s] : in[s];
-    if (ch.kind == GEMV_INNER && c < d.nb) v += corr[s];
-    xs[c] = v;
-  }
-  __syncthreads();
-  auto put = [&](int r, double v) {
-    const int o = gmem<const int32_t>(d.oslot)[r];
-    out[o] = ch.kind == GEMV_EDGE ? add[o] + v : v;
+  auto stage = [&]() {
+    for (int c = tid; c < d.cols; c += 256) {
+      const int s = gmem<const int32_t>(d.islot)[c];
+      double v = ch.kind == GEMV_EDGE ? corr[s] : in[s];
+      if (ch.kind == GEMV_INNER && c < d.nb) v += corr[s];
+      xs[c] = v;
+    }
+    __syncthreads();
   };
   const T *A = gmem<const T>(d.A);
+  const int32_t *os = gmem<const int32_t>(d.oslot) + ch.row0;
   if (!d.trans) {
-    // each wave works on four rows at once (independent sums keep four
-    // rows' loads in flight); rows past the band re-read the band's last
-    // row and are discarded
+    // each wave works on four rows at once; the next four 16-byte loads (of
+    // these rows or the next four) are issued before the products of the last
+    // ones, and a group's output slots one group ahead, so that the sums over
+    // the lanes and the stores run under them.  Rows past the band re-read the
+    // band's last row and are discarded.
+    constexpr int ST = 64 * VN;
     const int cv = d.cols / VN * VN;     // vectorised part (lda is a multiple of 4)
-    for (int rr0 = wid * 4; rr0 < ch.nrows; rr0 += 16) {
-      const T *row[4];
+    const int cl = max(cv - VN, 0);
+    typename VW::V cur[4], nxt[4];
+    auto load = [&](int rr, int c0, typename VW::V (&v)[4]) {
+      const int c = min(c0 + lane * VN, cl);
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        row[q] = A + (int64_t)(ch.row0 + min(rr0 + q, ch.nrows - 1)) * d.lda;
-      double acc[4] = {0.0, 0.0, 0.0, 0.0};
-      for (int c = lane * VN; c < cv; c += 64 * VN) {
-        typename VW::V v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const typename VW::V *>(row[q] + c);
+        v[q] = *reinterpret_cast<const typename VW::V *>(A + (int64_t)(ch.row0 + min(rr + q, ch.nrows - 1)) * d.lda + c);
+    };
+    auto slot = [&](int rr) { return os[min(rr + (lane >> 4), ch.nrows - 1)]; };   // lanes 16 q ..: row rr + q
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    int rr = wid * 4, c0 = 0;
+    load(rr, 0, cur);
+    int oc = slot(rr), on = slot(rr + 16);
+    stage();
+    double ac = ch.kind == GEMV_EDGE ? add[oc] : 0.0;
+    while (rr < ch.nrows) {
+      const bool last = c0 + ST >= cv;
+      const int rn = last ? rr + 16 : rr, cn = last ? 0 : c0 + ST;
+      if (rn < ch.nrows) load(rn, cn, nxt);
+      double an = 0.0;
+      int o2 = 0;
+      if (last && rn < ch.nrows) {
+        if (ch.kind == GEMV_EDGE) an = add[on];
+        o2 = slot(rn + 16);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      const int c = c0 + lane * VN;
+      if (c < cv) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           T e[VN];
-          VW::get(v[q], e);
+          VW::get(cur[q], e);
 #pragma unroll
           for (int u = 0; u < VN; ++u) acc[q] += double(e[u]) * xs[c + u];
         }
       }
-      for (int c = cv + lane; c < d.cols; c += 64)
+      if (last) {
+        for (int ct = cv + lane; ct < d.cols; ct += 64)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) acc[q] += double(row[q][c]) * xs[c];
+          for (int q = 0; q < 4; ++q)
+            acc[q] += double(A[(int64_t)(ch.row0 + min(rr + q, ch.nrows - 1)) * d.lda + ct]) * xs[ct];
+        const double sum = wave_sum4(acc);
+        if ((lane & 15) == 0 && rr + (lane >> 4) < ch.nrows) out[oc] = ch.kind == GEMV_EDGE ? ac + sum : sum;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc[q] = wsum(acc[q]);
-      if (lane == 0)
+        for (int q = 0; q < 4; ++q) acc[q] = 0.0;
+        oc = on;
+        ac = an;
+        on = o2;
+      }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (rr0 + q >= ch.nrows) break;
-          put(ch.row0 + rr0 + q, acc[q]);
-        }
+      for (int q = 0; q < 4; ++q) cur[q] = nxt[q];
+      rr = rn;
+      c0 = cn;
     }
   } else {
     // bands of GEMV_TROWS rows: lane = row, each wave takes every fourth
     // column (eight loads in flight per lane), the four sums meet in LDS
+    stage();
     double a = 0.0;
     const int r = ch.row0 + min(lane, ch.nrows - 1);
     const T *col = A + r;
@@ -128,8 +160,11 @@ __global__ __launch_bounds__(256) void k_gemv(const GemvDesc *__restrict__ items
     for (; c < d.cols; c += 4) a += double(col[(int64_t)c * d.lda]) * xs[c];
     part[tid] = a;
     __syncthreads();
-    if (tid < ch.nrows)
-      put(ch.row0 + tid, (part[tid] + part[tid + 64]) + (part[tid + 128] + part[tid + 192]));
+    if (tid < ch.nrows) {
+      const double v = (part[tid] + part[tid + 64]) + (part[tid + 128] + part[tid + 192]);
+      const int o = os[tid];
+      out[o] = ch.kind == GEMV_EDGE ? add[o] + v : v;
+    }
   }
 }
 
