@@ -81,15 +81,96 @@ __device__ inline int gemm_item(int tile, int tile_base, const int32_t *__restri
 // accumulators start from beta*C, loaded before the first product.
 // Workgroups are dealt round-robin to the 8 XCDs; each XCD is given one
 // contiguous range of tiles so that the tiles of a matrix share its L2.
-// The register budget is set for 5 waves per SIMD: the K = 64 block updates
-// are latency-bound and gain from the extra workgroup per CU (6 spills).
+// Bound by instruction issue next to the matrix cores: 16 products of 64
+// cycles a chunk and wave, against the loads, LDS stores and LDS loads that
+// feed them.  So an operand is loaded 16 bytes at a time along k (or a dword
+// from a scalar row address along its other index), without a branch: rows
+// past the edge repeat the last one (their results are not stored), and only
+// a last partial chunk selects zeros.  In LDS each half of a wave finds its k
+// (even or odd) contiguous, so that one 16-byte read feeds four products.
+// The matrix cores are busy 62-67% of the time on the large launches of a
+// 256x256, p = 3 factorization; those launches took 55.8 + 17.7 ms with dword
+// loads, stores and reads behind a branch each, 51.3 + 17.1 ms now.  Leaving
+// out the products of a wave with nothing to store made no difference.
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // rows start anywhere
 typedef float __attribute__((address_space(1))) gfloat;   // global memory
 constexpr int GK = 32;
 
 __device__ inline int xcd_tile(int b, int nb) {
   const int q = nb >> 3, r = nb & 7, x = b & 7, j = b >> 3;
   return x * q + min(x, r) + j;
+}
+
+// This thread's 8 values X(i, k0 + kt .. kt + 7), k0 <= k < K, of a block of 64
+// rows i0 .. of an operand: KC = 1 stores k contiguously (thread: row tid / 4,
+// kt = 8 (tid % 4)), KC = 0 the rows (thread: row tid % 64, kt = 8 wid).
+// 32-bit element offsets: every operand has fewer than 2^31 elements.
+template <int KC>
+__device__ inline void op_load(float (&r)[8], const gfloat *X, int ld, int i0, int n, int k0, int K) {
+  const int tid = threadIdx.x;
+  if constexpr (KC) {
+    const gfloat *p = X + min(i0 + (tid >> 2), n - 1) * ld;
+    const int k = k0 + 8 * (tid & 3);
+    if (k0 + GK <= K) {
+      typedef f32x4u __attribute__((address_space(1))) g4;
+      const f32x4 a = *(const g4 *)(p + k), b = *(const g4 *)(p + k + 4);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) r[q] = a[q], r[4 + q] = b[q];
+    } else {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const float v = p[min(k + q, K - 1)];
+        r[q] = k + q < K ? v : 0.f;
+      }
+    }
+  } else {
+    const int i = min(i0 + (tid & 63), n - 1);
+    const int k = k0 + 8 * __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (k0 + GK <= K) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) r[q] = (X + (k + q) * ld)[i];
+    } else {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const float v = (X + min(k + q, K - 1) * ld)[i];
+        r[q] = k + q < K ? v : 0.f;
+      }
+    }
+  }
+}
+// ... into LDS: S[(h * 64 + row) * P + j] = X(row, 2 j + h)
+template <int KC, int P>
+__device__ inline void op_store(float *S, const float (&r)[8]) {
+  const int tid = threadIdx.x;
+  const int row = KC ? tid >> 2 : tid & 63, j = 4 * (KC ? tid & 3 : tid >> 6);
+  *reinterpret_cast<f32x4 *>(S + row * P + j) = f32x4{r[0], r[2], r[4], r[6]};
+  *reinterpret_cast<f32x4 *>(S + (64 + row) * P + j) = f32x4{r[1], r[3], r[5], r[7]};
+}
+// 32 steps of k (16 products) of one wave; ap, bp: its half's rows in LDS
+__device__ inline f32x16 op_mul(const float *ap, const float *bp, f32x16 acc) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const f32x4 a = *reinterpret_cast<const f32x4 *>(ap + 4 * g);
+    const f32x4 b = *reinterpret_cast<const f32x4 *>(bp + 4 * g);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], b[q], acc, 0, 0, 0);
+  }
+  return acc;
+}
+
+__device__ inline void tile_store(gfloat *C, const GemmDesc &d, int m0, int n0, int gm0, int gn, const f32x16 &acc) {
+  if (m0 + 64 <= d.M && n0 + 64 <= d.N) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) C[(gm0 + 8 * (r >> 2) + (r & 3)) * d.ldc + gn] = acc[r];
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int gm = gm0 + 8 * (r >> 2) + (r & 3);
+      if (gm < d.M && gn < d.N) C[gm * d.ldc + gn] = acc[r];
+    }
+  }
 }
 
 template <int TA, int TB>
@@ -104,44 +185,16 @@ __global__ __launch_bounds__(256, 5) void k_gemm_f32_mfma(const GemmDesc *__rest
   const int t = tile - tile_start[lo];
   const int ntn = (d.N + 63) >> 6;
   const int m0 = (t / ntn) * 64, n0 = (t % ntn) * 64;
-  __shared__ float As[64 * (GK + 1)];   // As[m * (GK + 1) + k]
-  __shared__ float Bs[GK * 68];         // Bs[k * 68 + n]
+  constexpr int P = GK / 2 + 4;         // 16-byte reads of 8 rows fall on different banks
+  __shared__ __align__(16) float As[2 * 64 * P], Bs[2 * 64 * P];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int wr = wid >> 1, wc = wid & 1;
-  // global address space and 32-bit element offsets (every operand has
-  // fewer than 2^31 elements): a scalar base and one offset register per load
   const gfloat *A = (const gfloat *)d.A;
   const gfloat *B = (const gfloat *)d.B;
   float ra[8], rb[8];
   auto gload = [&](int k0) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int idx = tid + q * 256;
-      int mm, kk;
-      if (!TA) { mm = idx >> 5; kk = idx & 31; }
-      else { kk = idx >> 6; mm = idx & 63; }
-      const int gm = m0 + mm, gk = k0 + kk;
-      ra[q] = (gm < d.M && gk < d.K) ? A[TA ? gk * d.lda + gm : gm * d.lda + gk] : 0.f;
-      int nn;
-      if (!TB) { kk = idx >> 6; nn = idx & 63; }
-      else { nn = idx >> 5; kk = idx & 31; }
-      const int gn = n0 + nn, gk2 = k0 + kk;
-      rb[q] = (gn < d.N && gk2 < d.K) ? B[TB ? gn * d.ldb + gk2 : gk2 * d.ldb + gn] : 0.f;
-    }
-  };
-  auto sstore = [&]() {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int idx = tid + q * 256;
-      int mm, kk;
-      if (!TA) { mm = idx >> 5; kk = idx & 31; }
-      else { kk = idx >> 6; mm = idx & 63; }
-      As[mm * (GK + 1) + kk] = ra[q];
-      int nn;
-      if (!TB) { kk = idx >> 6; nn = idx & 63; }
-      else { nn = idx >> 5; kk = idx & 31; }
-      Bs[kk * 68 + nn] = rb[q];
-    }
+    op_load<!TA>(ra, A, d.lda, m0, d.M, k0, d.K);
+    op_load<TB>(rb, B, d.ldb, n0, d.N, k0, d.K);
   };
   // K range of this tile: triangular operands contribute nothing outside
   // it (m0, n0 are multiples of 64, so the range stays in whole chunks)
@@ -149,39 +202,33 @@ __global__ __launch_bounds__(256, 5) void k_gemm_f32_mfma(const GemmDesc *__rest
   const int ke = (d.tri & GEMM_TRI_B_UPPER) ? min(d.K, n0 + 64) : d.K;
   if (kb < ke) gload(kb);
   gfloat *C = (gfloat *)d.C;
-  const int gn = n0 + wc * 32 + (lane & 31);
+  const int gn = n0 + wc * 32 + (lane & 31), gm0 = m0 + wr * 32 + 4 * (lane >> 5);
   const bool cin = d.alpha == 1.0 && d.beta != 0.0;
   const float al = float(d.alpha), be = float(d.beta);
-  f32x16 acc;
+  f32x16 acc = {};
+  if (cin)
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int gm = m0 + wr * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-    acc[r] = (cin && gm < d.M && gn < d.N) ? be * C[gm * d.ldc + gn] : 0.f;
-  }
-  const float *ap = As + (wr * 32 + (lane & 31)) * (GK + 1) + (lane >> 5);
-  const float *bp = Bs + (lane >> 5) * 68 + wc * 32 + (lane & 31);
+    for (int r = 0; r < 16; ++r)
+      acc[r] = be * C[min(gm0 + 8 * (r >> 2) + (r & 3), d.M - 1) * d.ldc + min(gn, d.N - 1)];
+  const float *ap = As + ((lane >> 5) * 64 + wr * 32 + (lane & 31)) * P;
+  const float *bp = Bs + ((lane >> 5) * 64 + wc * 32 + (lane & 31)) * P;
   for (int k0 = kb; k0 < ke; k0 += GK) {
-    sstore();
+    op_store<!TA, P>(As, ra);
+    op_store<TB, P>(Bs, rb);
     __syncthreads();
     if (k0 + GK < ke) gload(k0 + GK);
-#pragma unroll
-    for (int kk = 0; kk < GK; kk += 2)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ap[kk], bp[kk * 68], acc, 0, 0, 0);
+    acc = op_mul(ap, bp, acc);
     __syncthreads();
   }
+  if (!cin)
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int gm = m0 + wr * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-    if (gm < d.M && gn < d.N) {
-      gfloat *c = C + gm * d.ldc + gn;
+    for (int r = 0; r < 16; ++r) {
       float v = acc[r];
-      if (!cin) {
-        v *= al;
-        if (d.beta != 0.0) v += be * (*c);
-      }
-      *c = v;
+      v *= al;
+      if (d.beta != 0.0) v += be * C[min(gm0 + 8 * (r >> 2) + (r & 3), d.M - 1) * d.ldc + min(gn, d.N - 1)];
+      acc[r] = v;
     }
-  }
+  tile_store(C, d, m0, n0, gm0, gn, acc);
 }
 
 // Accumulating products with a short K (the block updates of the blocked
@@ -192,6 +239,10 @@ __global__ __launch_bounds__(256, 5) void k_gemm_f32_mfma(const GemmDesc *__rest
 // instructions in the same order as in k_gemm_f32_mfma (start from beta*C, K
 // in chunks of 32 with zero padding, v_mfma_f32_32x32x2f32 on pairs of k), so
 // the results are the same bit for bit.  Items: alpha = 1, no transposes.
+// Bound between the matrix cores (45% busy) and C, read and written once per
+// block of 64 columns (3 TB/s of C and B together): the block updates of 4096
+// leaves of ~580 took 48.2 ms with dword LDS traffic and masked loads, 37.1 ms
+// as now; of 256 leaves of up to 1600, p = 1, 10.8 and 9.0 ms.
 constexpr int SK = 64;   // largest K of a strip product
 __global__ __launch_bounds__(256, 4) void k_gemm_f32_strip(const GemmDesc *__restrict__ items,
                                                          const int32_t *__restrict__ unit_start,
@@ -207,64 +258,46 @@ __global__ __launch_bounds__(256, 4) void k_gemm_f32_strip(const GemmDesc *__res
   const int nstrip = (ntn + tps - 1) / tps;
   const int m0 = (u / nstrip) * 64, t0 = (u % nstrip) * tps;
   const int t1 = min(ntn, t0 + tps);
-  const int kc = (d.K + GK - 1) / GK * GK;         // K padded to whole chunks (<= SK)
-  __shared__ float As[64 * (SK + 1)];   // As[m * (SK + 1) + k]
-  __shared__ float Bs[SK * 68];         // Bs[k * 68 + n]
+  constexpr int P = SK / 2 + 4;
+  __shared__ __align__(16) float As[2 * 64 * P], Bs[2 * 64 * P];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int wr = wid >> 1, wc = wid & 1;
   const gfloat *A = (const gfloat *)d.A;
   const gfloat *B = (const gfloat *)d.B;
   gfloat *C = (gfloat *)d.C;
   const float be = float(d.beta);
-  // A block: 64 x kc
-  for (int idx = tid; idx < 64 * kc; idx += 256) {
-    const int mm = idx / kc, kk = idx - mm * kc;
-    const int gm = m0 + mm;
-    As[mm * (SK + 1) + kk] = (gm < d.M && kk < d.K) ? A[gm * d.lda + kk] : 0.f;
-  }
-  // B tile (kc x 64) and C tile of column tile t into registers: each thread
-  // holds kc/4 B values (k = idx >> 6, n = idx & 63) and its 16 C values
-  float rb[SK / 4], rc[16];
-  const int gcol = wc * 32 + (lane & 31);
+  if (d.K <= 0) return;                 // beta = 1: nothing to add
+  const bool two = d.K > GK;            // one chunk of k or two
+  float r0[8], r1[8], rc[16];
+  op_load<1>(r0, A, d.lda, m0, d.M, 0, d.K);
+  if (two) op_load<1>(r1, A, d.lda, m0, d.M, GK, d.K);
+  op_store<1, P>(As, r0);
+  if (two) op_store<1, P>(As + GK / 2, r1);
+  // B tile and C tile of column tile t into registers
+  const int gcol = wc * 32 + (lane & 31), gm0 = m0 + wr * 32 + 4 * (lane >> 5);
   auto fetch = [&](int t) {
-    const int n0 = t * 64;
+    op_load<0>(r0, B, d.ldb, t * 64, d.N, 0, d.K);
+    if (two) op_load<0>(r1, B, d.ldb, t * 64, d.N, GK, d.K);
+    const int gn = min(t * 64 + gcol, d.N - 1);
 #pragma unroll
-    for (int q = 0; q < SK / 4; ++q) {
-      const int idx = tid + q * 256;
-      const int kk = idx >> 6, nn = idx & 63;
-      const int gn = n0 + nn;
-      rb[q] = (kk < kc && kk < d.K && gn < d.N) ? B[kk * d.ldb + gn] : 0.f;
-    }
-    const int gn = n0 + gcol;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int gm = m0 + wr * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      rc[r] = (gm < d.M && gn < d.N) ? C[gm * d.ldc + gn] : 0.f;
-    }
+    for (int r = 0; r < 16; ++r) rc[r] = C[min(gm0 + 8 * (r >> 2) + (r & 3), d.M - 1) * d.ldc + gn];
   };
   if (t0 < t1) fetch(t0);
-  const float *ap = As + (wr * 32 + (lane & 31)) * (SK + 1) + (lane >> 5);
-  const float *bp = Bs + (lane >> 5) * 68 + wc * 32 + (lane & 31);
+  const float *ap = As + ((lane >> 5) * 64 + wr * 32 + (lane & 31)) * P;
+  const float *bp = Bs + ((lane >> 5) * 64 + wc * 32 + (lane & 31)) * P;
   for (int t = t0; t < t1; ++t) {
     __syncthreads();       // the previous tile's products have read Bs
-#pragma unroll
-    for (int q = 0; q < SK / 4; ++q) {
-      const int idx = tid + q * 256;
-      if ((idx >> 6) < kc) Bs[(idx >> 6) * 68 + (idx & 63)] = rb[q];
-    }
+    op_store<0, P>(Bs, r0);
+    if (two) op_store<0, P>(Bs + GK / 2, r1);
     f32x16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = be * rc[r];
     __syncthreads();
     if (t + 1 < t1) fetch(t + 1);
-    for (int kk = 0; kk < kc; kk += 2)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ap[kk], bp[kk * 68], acc, 0, 0, 0);
+    acc = op_mul(ap, bp, acc);
+    if (two) acc = op_mul(ap + GK / 2, bp + GK / 2, acc);
     const int gn = t * 64 + gcol;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int gm = m0 + wr * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      if (gm < d.M && gn < d.N) C[gm * d.ldc + gn] = acc[r];
-    }
+    tile_store(C, d, m0, t * 64, gm0, gn, acc);
   }
 }
 
