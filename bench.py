@@ -519,11 +519,12 @@ def main():
         "algorithmic_bytes": "8 nnzb b^2 + 4 nnzb + 4 (K+1) + 16 N"}
     ap_ = r["apply"]
     out["roofline_apply"] = {
-        "kernel": "M^-1 r sweeps (k_gemv, k_pull, k_slot_copy replayed from a hipGraph)",
+        "kernel": "M^-1 r sweeps (k_gemv, k_pull, k_level replayed from a hipGraph)",
         "bound": "hbm", "achieved": ap_["GBs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": ap_["GBs"] / HBM_PEAK_GBS, "bytes_per_apply": ap_["bytes"],
         "avg_apply_ms": ap_["avg_ms"], "applies": ap_["n"],
-        "algorithmic_bytes": "every stored factor entry once per apply (A_ss^-1 in both sweeps) "
+        "algorithmic_bytes": "every stored factor entry once per apply (of A_ss^-1 also the "
+                             "columns next to separators a second time) "
                              "in factor precision + 16 N for the FP64 vector in and out"}
     g = r["mfma"]
     out["roofline_factor_mfma"] = {

@@ -242,7 +242,7 @@ __global__ __launch_bounds__(256, 5) void k_gemm_f32_mfma(const GemmDesc *__rest
 // Bound between the matrix cores (45% busy) and C, read and written once per
 // block of 64 columns (3 TB/s of C and B together): the block updates of 4096
 // leaves of ~580 took 48.2 ms with dword LDS traffic and masked loads, 37.1 ms
-// as now; of 256 leaves of up to 1600, p = 1, 10.8 and 9.0 ms.
+// as now; at 160x120, p = 1, 10.8 and 9.0 ms.
 constexpr int SK = 64;   // largest K of a strip product
 __global__ __launch_bounds__(256, 4) void k_gemm_f32_strip(const GemmDesc *__restrict__ items,
                                                          const int32_t *__restrict__ unit_start,
