@@ -959,56 +959,6 @@ __device__ inline int wave_argmax_key(uint64_t key, bool can, uint64_t *kmax) {
 }
 
 // ------------------------------------------------------------------ fused block elimination
-// s[0..7] += h * p_l for the lanes l = R..R+7 of every row of 16 lanes of p:
-// a value that the lanes of a wave hold once per 16 lanes multiplies every
-// lane's h without a trip through LDS (DPP row_newbcast).  The wait states
-// cover a p that was computed right before.
-template <int R>
-__device__ inline void fmac8(float *s, float p, float h) {
-  static_assert(R == 0 || R == 8, "half rows");
-#define FMAC_ROW(i, l) "v_fmac_f32_dpp %" #i ", %8, %9 row_newbcast:" #l " row_mask:0xf bank_mask:0xf\n\t"
-  if constexpr (R == 0)
-    asm("s_nop 1\n\t" FMAC_ROW(0, 0) FMAC_ROW(1, 1) FMAC_ROW(2, 2) FMAC_ROW(3, 3) FMAC_ROW(4, 4)
-            FMAC_ROW(5, 5) FMAC_ROW(6, 6) FMAC_ROW(7, 7)
-        : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7])
-        : "v"(p), "v"(h));
-  else
-    asm("s_nop 1\n\t" FMAC_ROW(0, 8) FMAC_ROW(1, 9) FMAC_ROW(2, 10) FMAC_ROW(3, 11) FMAC_ROW(4, 12)
-            FMAC_ROW(5, 13) FMAC_ROW(6, 14) FMAC_ROW(7, 15)
-        : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7])
-        : "v"(p), "v"(h));
-#undef FMAC_ROW
-}
-template <int R>
-__device__ inline void fmac8(double *s, double p, double h) {
-  static_assert(R == 0 || R == 8, "half rows");
-#define FMAC_ROW(i, l) "v_fmac_f64_dpp %" #i ", %8, %9 row_newbcast:" #l " row_mask:0xf bank_mask:0xf\n\t"
-  if constexpr (R == 0)
-    asm("s_nop 1\n\t" FMAC_ROW(0, 0) FMAC_ROW(1, 1) FMAC_ROW(2, 2) FMAC_ROW(3, 3) FMAC_ROW(4, 4)
-            FMAC_ROW(5, 5) FMAC_ROW(6, 6) FMAC_ROW(7, 7)
-        : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7])
-        : "v"(p), "v"(h));
-  else
-    asm("s_nop 1\n\t" FMAC_ROW(0, 8) FMAC_ROW(1, 9) FMAC_ROW(2, 10) FMAC_ROW(3, 11) FMAC_ROW(4, 12)
-            FMAC_ROW(5, 13) FMAC_ROW(6, 14) FMAC_ROW(7, 15)
-        : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7])
-        : "v"(p), "v"(h));
-#undef FMAC_ROW
-}
-// the same for the four lanes 4..7
-__device__ inline void fmac4(float *s, float p, float h) {
-#define FMAC_ROW(i, l) "v_fmac_f32_dpp %" #i ", %4, %5 row_newbcast:" #l " row_mask:0xf bank_mask:0xf\n\t"
-  asm("s_nop 1\n\t" FMAC_ROW(0, 4) FMAC_ROW(1, 5) FMAC_ROW(2, 6) FMAC_ROW(3, 7)
-      : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]) : "v"(p), "v"(h));
-#undef FMAC_ROW
-}
-__device__ inline void fmac4(double *s, double p, double h) {
-#define FMAC_ROW(i, l) "v_fmac_f64_dpp %" #i ", %4, %5 row_newbcast:" #l " row_mask:0xf bank_mask:0xf\n\t"
-  asm("s_nop 1\n\t" FMAC_ROW(0, 4) FMAC_ROW(1, 5) FMAC_ROW(2, 6) FMAC_ROW(3, 7)
-      : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]) : "v"(p), "v"(h));
-#undef FMAC_ROW
-}
-
 // One workgroup eliminates the block columns [k0, k0 + wb), wb <= BW, of
 // one matrix and applies them to the whole column window [k0, k0 + BW)
 // (columns past n exist for LU on [A | I]); one row per thread

@@ -1,5 +1,6 @@
 // Sums of doubles over the lanes of a wave (gfx950, wave64), in the order of
-// a tree over lane ^ 32, 16, 8, 4, 2, 1.
+// a tree over lane ^ 32, 16, 8, 4, 2, 1, and multiply-adds with a value of
+// another lane.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -67,5 +68,44 @@ __device__ inline double wave_sum4(const double (&v)[4]) {
   s = add_xor<2>(s);
   return add_xor<1>(s);
 }
+
+// s[0..7] += h * p_l for the lanes l = R..R+7 of every row of 16 lanes of p:
+// a value that the lanes of a wave hold once per 16 lanes multiplies every
+// lane's h without a trip through LDS (DPP row_newbcast).  The wait states
+// cover a p that was computed right before.  The sums are early clobbers: the
+// first instruction writes one while the later ones still read p and h, which
+// must not share its register (they would where they hold the same value).
+#define FMAC_ROW(w, i, p, h, l) \
+  "v_fmac_f" #w "_dpp %" #i ", %" #p ", %" #h " row_newbcast:" #l " row_mask:0xf bank_mask:0xf\n\t"
+#define FMAC_8(w, l0, l1, l2, l3, l4, l5, l6, l7)                                                \
+  asm("s_nop 1\n\t" FMAC_ROW(w, 0, 8, 9, l0) FMAC_ROW(w, 1, 8, 9, l1) FMAC_ROW(w, 2, 8, 9, l2)   \
+          FMAC_ROW(w, 3, 8, 9, l3) FMAC_ROW(w, 4, 8, 9, l4) FMAC_ROW(w, 5, 8, 9, l5)             \
+              FMAC_ROW(w, 6, 8, 9, l6) FMAC_ROW(w, 7, 8, 9, l7)                                  \
+      : "+&v"(s[0]), "+&v"(s[1]), "+&v"(s[2]), "+&v"(s[3]), "+&v"(s[4]), "+&v"(s[5]),            \
+        "+&v"(s[6]), "+&v"(s[7])                                                                 \
+      : "v"(p), "v"(h))
+#define FMAC_4(w)                                                                                \
+  asm("s_nop 1\n\t" FMAC_ROW(w, 0, 4, 5, 4) FMAC_ROW(w, 1, 4, 5, 5) FMAC_ROW(w, 2, 4, 5, 6)      \
+          FMAC_ROW(w, 3, 4, 5, 7)                                                                \
+      : "+&v"(s[0]), "+&v"(s[1]), "+&v"(s[2]), "+&v"(s[3])                                       \
+      : "v"(p), "v"(h))
+template <int R>
+__device__ inline void fmac8(float *s, float p, float h) {
+  static_assert(R == 0 || R == 8, "half rows");
+  if constexpr (R == 0) FMAC_8(32, 0, 1, 2, 3, 4, 5, 6, 7);
+  else FMAC_8(32, 8, 9, 10, 11, 12, 13, 14, 15);
+}
+template <int R>
+__device__ inline void fmac8(double *s, double p, double h) {
+  static_assert(R == 0 || R == 8, "half rows");
+  if constexpr (R == 0) FMAC_8(64, 0, 1, 2, 3, 4, 5, 6, 7);
+  else FMAC_8(64, 8, 9, 10, 11, 12, 13, 14, 15);
+}
+// the same for the four lanes 4..7
+__device__ inline void fmac4(float *s, float p, float h) { FMAC_4(32); }
+__device__ inline void fmac4(double *s, double p, double h) { FMAC_4(64); }
+#undef FMAC_4
+#undef FMAC_8
+#undef FMAC_ROW
 
 }  // namespace spand
