@@ -33,6 +33,7 @@
 #include <numeric>
 #include <set>
 
+#include "elim_launches.h"
 #include "factor.h"
 
 namespace spand {
@@ -477,45 +478,13 @@ int Factor::elim_batch(std::vector<ElimDesc> &items, int mode) {
   // pivot rows of the other columns out to TB
   auto eliminate_block = [&](int k0) -> int {
     if (fused) {
-      // one launch per 64-row size class (items are sorted by n, descending),
-      // so that no workgroup carries waves without rows.  The class with
-      // the most rows runs on the build stream, the others at the same time
-      // on a second one (independent matrices): a class of a few large
-      // matrices would otherwise hold the whole device for its long chain
-      // of dependent steps.  Classes that follow each other on a stream and
-      // have no more matrices together than the device has compute units go
-      // into one launch: they would leave most units idle one after another
-      // (16x16 p = 1 FP64, four leaves in four classes: elimination 6.8 ->
-      // 3.2 ms).
+      // the launch with the most rows on the build stream, the others at the
+      // same time on a second one (independent matrices): a class of a few
+      // large matrices would otherwise hold the whole device for its long
+      // chain of dependent steps
       const int na = nactive_at(k0);
-      std::vector<std::pair<int, int>> cls;
-      for (int a = 0; a < na;) {
-        int b = a + 1;
-        while (b < na && cdiv(items[b].n, 64) == cdiv(items[a].n, 64)) ++b;
-        cls.push_back({a, b});
-        a = b;
-      }
-      size_t big = 0;
-      for (size_t c = 1; c < cls.size(); ++c)
-        if (int64_t(cls[c].second - cls[c].first) * items[cls[c].first].n >
-            int64_t(cls[big].second - cls[big].first) * items[cls[big].first].n)
-          big = c;
-      constexpr int kUnits = 256;
-      if (na <= kUnits) {
-        cls.assign(1, {0, na});
-        big = 0;
-      } else {
-        const int b0 = cls[big].first, b1 = cls[big].second;
-        if (b0 > 0 && b0 <= kUnits) {
-          cls.erase(cls.begin(), cls.begin() + big);
-          cls.insert(cls.begin(), {0, b0});
-          big = 1;
-        }
-        if (b1 < na && na - b1 <= kUnits) {
-          cls.resize(big + 1);
-          cls.push_back({b1, na});
-        }
-      }
+      size_t big;
+      const auto cls = elim_launches(na, [&](int i) { return items[size_t(i)].n; }, &big);
       if (cls.size() == 1 || one_stream) {
         for (const auto &c : cls)
           SP_TRY(launch_elim_block(ft, d_items + c.first, c.second - c.first, k0, mode,
