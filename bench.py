@@ -523,9 +523,11 @@ def main():
         "bound": "hbm", "achieved": ap_["GBs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": ap_["GBs"] / HBM_PEAK_GBS, "bytes_per_apply": ap_["bytes"],
         "avg_apply_ms": ap_["avg_ms"], "applies": ap_["n"],
-        "algorithmic_bytes": "every stored factor entry once per apply (of A_ss^-1 also the "
-                             "columns next to separators a second time) "
-                             "in factor precision + 16 N for the FP64 vector in and out"}
+        "algorithmic_bytes": "in factor precision: n^2 + e^2 elements of every leaf's inverse "
+                             "(e of its n unknowns next to a separator), 2 n^2 of every other "
+                             "interior's (n^2 at the top), the couplings, F_s and B_s once; "
+                             "+ 16 N for the FP64 vector in and out.  Products that fused "
+                             "launches recompute are not counted"}
     g = r["mfma"]
     out["roofline_factor_mfma"] = {
         "kernel": "factorization products on the matrix cores (k_gemm_f32_mfma / "
@@ -654,7 +656,7 @@ def run_steps(sp, torch, dA, db, dxs, cfg, eps, L, dtype, s, m, schedule, steps,
     spmv_ms = sum(i.t_spmv_ms for i in infos)
     spmv_n = sum(i.n_spmv for i in infos)
     spmv_avg = spmv_ms / max(spmv_n, 1)
-    # apply: every stored factor entry once per application + FP64 vector in/out
+    # apply: the stored bytes that one application reads + FP64 vector in/out
     app_bytes = float(sts[-1]["factor_bytes"]) + 16.0 * N
     app_ms = sum(i.t_apply_ms for i in infos)
     app_n = sum(i.n_apply for i in infos)

@@ -143,7 +143,14 @@ typedef struct {
   int64_t size_before[SPAND_MAX_LEVELS];  /* sum |s| before sparsification  */
   int64_t size_after[SPAND_MAX_LEVELS];   /* sum k after sparsification      */
   int32_t top_size;                       /* unknowns left at the top        */
-  int64_t factor_bytes;                   /* device bytes read by one apply  */
+  int64_t factor_bytes;                   /* stored bytes read by one apply:
+                                             n^2 + e^2 elements of a leaf's
+                                             inverse (e of its n unknowns next
+                                             to a separator), 2 n^2 of another
+                                             interior's (n^2 where nothing is
+                                             coupled to it: the top), all
+                                             other blocks once; what a fused
+                                             launch recomputes not counted  */
   double factor_flops;                    /* algorithmic flops of the factor */
   double t_host_ms;                       /* host ND + planning              */
   double t_device_ms;                     /* device phases (event timed)     */

@@ -1502,7 +1502,8 @@ int Factor::eliminate_dense(int l, LevelState &S, LevelSource &src) {
     d.ld = n;
     d.pad = s;                   // owner cluster (elim_batch reorders the items)
     items.push_back(d);
-    acct(csys(l, s), double(n) * n * tsz * 2, 2.0 * double(n) * n * n);   // A_ss^-1: both sweeps
+    // A_ss^-1: both sweeps, the backward one alone where nothing is coupled (the top)
+    acct(csys(l, s), double(n) * n * tsz * (nb[s].empty() ? 1 : 2), 2.0 * double(n) * n * n);
   }
   SP_TRY(elim_batch(items, 0));
   trace("elim enqueue", l);
