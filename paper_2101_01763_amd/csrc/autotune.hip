@@ -114,8 +114,10 @@ int tuned_gemv_rows(FType t, int bs) {
   return it == g_gemv.end() ? 0 : it->second;
 }
 
-// Times the forward sweep GEMV of one level with each band height and keeps
-// the fastest for (precision, bs).  `sets` builds a GemvSet for a band height.
+// Times the products with the whole leaf inverses with each band height and
+// keeps the fastest for (precision, bs); `build` makes the set of a height.
+// The sweeps' own level-0 launches take parts of the same matrices (the rows
+// next to separators, then the rest), which are not timed here.
 int autotune_gemv(FType t, int bs, const std::function<int(int, GemvSet &)> &build,
                   double *in, double *out, hipStream_t st, int *rows_out) {
   {
@@ -127,9 +129,10 @@ int autotune_gemv(FType t, int bs, const std::function<int(int, GemvSet &)> &bui
       return SPAND_OK;
     }
   }
-  // 128-row bands can win on the level-0 matrices timed here by a hair
-  // but lose more on the smaller matrices of the upper levels (measured at
-  // 4M unknowns: 148 ms of sweeps per solve against 140-141 for 32 or 64)
+  // 32 or 64: the interfaces' F_s and B_s of level 0 take the same height, and
+  // bands of 128 rows lose more on such smaller matrices than they can win on
+  // the leaves (measured when the levels above took it too: 148 ms of sweeps
+  // per solve at 4M unknowns against 140-141)
   int best = 64;
   float bt = 1e30f;
   for (int R : {32, 64}) {

@@ -15,8 +15,13 @@ constexpr int ELIM_UNITS = 256;   // compute units of the device
 // rows; *big is the range with the most rows.  Classes that follow each other
 // on a stream (those before *big and those after it) and have no more matrices
 // together than the device has compute units go into one launch: they would
-// leave most units idle one after another (16x16 p = 1 FP64, four leaves in
-// four classes: elimination 6.8 -> 3.2 ms).
+// leave most units idle one after another.  Factorization with a launch per
+// class / with joined launches, in ms: 16x16 p = 1 FP64 (four leaves in four
+// classes) 10.0 / 6.8, 40x40 p = 1 FP64 15.9 / 12.6, 61x47 p = 2 FP64 23.1 /
+// 21.5, 91x69 p = 3 FP64 63.8 / 62.3, 128x128 p = 2 FP32 58.6 / 56.6, 160x120
+// p = 1 FP32 36.7 / 36.1, batches of 6 to 36 systems of several sizes 22-39 /
+// 18-32.  A small matrix runs in a workgroup as wide as the largest of its
+// launch, which has the longer chain of steps anyway.
 template <typename Rows>
 std::vector<std::pair<int, int>> elim_launches(int na, const Rows &rows, size_t *big) {
   std::vector<std::pair<int, int>> cls;

@@ -1187,7 +1187,8 @@ int Factor::level0(const NDResult &nd, LevelState &S) {
       // A_ss^-1: the parts the two sweeps read
       acct(csys(0, s), (double(S.size[s]) * S.size[s] + double(d.nb) * d.nb) * tsz, 0.0);
     }
-    // band height of the sweep GEMVs: autotuned once per (precision, b)
+    // band height of the sweep GEMVs: autotuned once per (precision, b), on
+    // whole inverses (the sweeps launch parts of them, see k_gemv)
     defer([this, &AL, gv, vs]() -> int {
       void *tin;
       SP_TRY(dalloc(&tin, size_t(N) * 8, false));
@@ -1338,17 +1339,27 @@ void LevelSet::add(const void *M, int ldm, const int32_t *slots, int size, int r
 // and the neighbours' products of the first step recomputed in the same
 // workgroup (c).  One launch costs about 5 us whatever it does, and one
 // compute unit draws about 100 GB/s, so the choice goes by the largest
-// matrix of the level and the number of clusters (apply in us at 128x128
-// p = 2 FP32, 96x96 p = 2 FP32 eps = 1e-3, 160x120 p = 1 FP32):
-//   all (a)          866, 672, 610
-//   all (b)          880, 683, 573
-//   all (c)          878, 714, 551
-//   the rules below  860, 681, 543
-// (c) pays while the repeated matrices are small (up to 64 KB, 128 unknowns
-// in FP32) and the level has too few clusters to fill the device; beyond
-// 256 KB a cluster per workgroup loses to bands of rows.  Workgroups of 1024
-// threads where the clusters do not fill the device (256 threads: 1020 us
-// instead of 860).
+// matrix of the level and the number of clusters.  Apply and transposed apply
+// in us (whole sweeps, level 0 included; eps = 1e-2, but 1e-1 at 160x120):
+//                             all (a)     all (b)     all (c)   the rules below
+//   160x120 p = 1 FP32       453,  466   421,  446   395,  426   396,  425
+//   160x120 p = 1 FP64       639,  668   606,  643   579,  624   578,  623
+//   128x128 p = 2 FP32       766,  849   749,  850   750,  876   742,  848
+//   128x128 p = 2 FP64      1165, 1234  1155, 1254  1162, 1306  1156, 1256
+//   91x69 p = 3 FP64         800,  843   790,  867   807,  929   791,  854
+//   192x192 p = 2 FP32      1437, 1627  1423, 1637  1444, 1675  1418, 1633
+//   192x192 p = 2 FP64      2364, 2489  2353, 2514  2381, 2594  2353, 2513
+//   37x29 p = 1 FP32         118,  154   121,  167   124,  175   121,  167
+//   37x29 p = 1 FP64         134,  159   139,  183   145,  200   133,  164
+//   96x96 p = 2, 1e-3 FP32   566,  663   578,  680   603,  753   578,  679
+//   96x96 p = 2, 1e-3 FP64   854,  908   906, 1025   951, 1145   860,  921
+// (c) pays where many levels have small matrices (p = 1: up to 64 KB, 128
+// unknowns in FP32) and too few clusters to fill the device; beyond 256 KB a
+// cluster per workgroup loses to bands of rows, clearly so in FP64 and
+// transposed.  The rules are within 2.5% of the best column but for the smallest
+// plans (up to 8% behind (a) at 37x29).  Workgroups of 1024 threads where the
+// clusters do not fill the device (256 threads: 1020, not 860 us, for 128x128
+// p = 2 FP32 with whole leaf inverses).
 int Factor::level_plan(ApplyLevel &AL, const LevelSource &src) {
   const size_t tsz = fsize(ft);
   size_t big = 0;
@@ -1362,8 +1373,8 @@ int Factor::level_plan(ApplyLevel &AL, const LevelSource &src) {
     byn[c.n].push_back(&c);
     bys[c.s].push_back(&c);
   }
-  // rows of a band: 32 (16: 4079 us instead of 3876 at 256x256 p = 3; 64:
-  // 966 instead of 866 at 128x128 p = 2)
+  // rows of a band: 32 (16: 4079, not 3876 us at 256x256 p = 3; 64: 966, not
+  // 866 us at 128x128 p = 2, all (a), FP32 with whole leaf inverses)
   constexpr int band = 32;
   auto banded = [&](LevelSet &L, const void *M, int ldm, const int32_t *slots, int size, int base,
                     const std::vector<LevelItem> &its) {
@@ -2218,8 +2229,8 @@ int Factor::sparsify(int l, const NDResult &nd, LevelState &S, LevelState &Nx, L
   trace("merge plan", l);
   // the sweep sets queued by this level (compression) are built while the
   // host next waits for the device, before the next level's rank read-back:
-  // the device goes on to the next level's eliminations meanwhile (the
-  // caller keeps S, whose slot lists they read, alive until then)
+  // the device goes on to the next level's eliminations meanwhile (they hold
+  // copies of all host data they need)
   return SPAND_OK;
 }
 

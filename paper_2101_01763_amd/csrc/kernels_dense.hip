@@ -89,9 +89,9 @@ __device__ inline int gemm_item(int tile, int tile_base, const int32_t *__restri
 // a last partial chunk selects zeros.  In LDS each half of a wave finds its k
 // (even or odd) contiguous, so that one 16-byte read feeds four products.
 // The matrix cores are busy 62-67% of the time on the large launches of a
-// 256x256, p = 3 factorization; those launches took 55.8 + 17.7 ms with dword
-// loads, stores and reads behind a branch each, 51.3 + 17.1 ms now.  Leaving
-// out the products of a wave with nothing to store made no difference.
+// 256x256, p = 3 factorization; those launches take 51.3 + 17.1 ms, and 55.8 +
+// 17.7 ms with dword loads, stores and reads behind a branch each.  Leaving out
+// the products of a wave with nothing to store makes no difference.
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // rows start anywhere
@@ -241,8 +241,8 @@ __global__ __launch_bounds__(256, 5) void k_gemm_f32_mfma(const GemmDesc *__rest
 // the results are the same bit for bit.  Items: alpha = 1, no transposes.
 // Bound between the matrix cores (45% busy) and C, read and written once per
 // block of 64 columns (3 TB/s of C and B together): the block updates of 4096
-// leaves of ~580 took 48.2 ms with dword LDS traffic and masked loads, 37.1 ms
-// as now; at 160x120, p = 1, 10.8 and 9.0 ms.
+// leaves of ~580 take 37.1 ms, and 48.2 ms with dword LDS traffic and masked
+// loads; at 160x120, p = 1, 9.0 and 10.8 ms.
 constexpr int SK = 64;   // largest K of a strip product
 __global__ __launch_bounds__(256, 4) void k_gemm_f32_strip(const GemmDesc *__restrict__ items,
                                                          const int32_t *__restrict__ unit_start,
@@ -982,14 +982,14 @@ __device__ inline int wave_argmax_key(uint64_t key, bool can, uint64_t *kmax) {
 //   Bound by the latency of a step's chain (wave maximum 120 cycles, two trips
 // through LDS 75 each, division 65, ...: about 0.4 us a step of a single
 // wave) and by the slots' multiply-adds (64 of 4.6 cycles per wave and step).
-// One workgroup of 1024 threads, FP64, 32 columns: 106 -> 63 us; 3906 FP32
-// matrices of 576 rows, 64 columns: 2.10 -> 1.63 ms; LU of 4128 of 256 rows:
-// 1.68 -> 0.68 ms (of it 0.9 ms by writing the LU's two row parts as 16-byte
-// vectors).  Before, every step carried whole rows through LDS (each wave's
-// candidate written, the pivot row read back by every lane).  Two panels of
-// code per trip round the loop (no slot rotation between them) were slower
-// (instruction fetch), and so was a bound of 96 registers for a second
-// workgroup per compute unit (spills: 1.85 ms).
+// One workgroup of 1024 threads, FP64, 32 columns: 63 us; 3906 FP32 matrices
+// of 576 rows, 64 columns: 1.63 ms; LU of 4128 of 256 rows: 0.68 ms.  With
+// every step carrying whole rows through LDS (each wave's candidate written,
+// the pivot row read back by every lane): 106 us, 2.10 ms and 1.68 ms (0.9 ms
+// of the last from the LU's two row parts written element by element, not as
+// 16-byte vectors).  Two panels of code per trip round the loop (no slot
+// rotation between them) are slower (instruction fetch), and so is a bound of
+// 96 registers for a second workgroup per compute unit (spills: 1.85 ms).
 //   MODE 0/2: Gauss-Jordan (with / without pivoting); every row changes,
 //             the pivot row is scaled; on exit the block columns are the
 //             block's P_B.
@@ -1273,27 +1273,27 @@ __global__ __launch_bounds__(MAXT) void k_elim_block(const ElimDesc *__restrict_
         }
       } else {
 #pragma unroll
-      for (int i = 0; i < BW; ++i) {
-        const int col = (nsteps + i) & (BW - 1);
-        if (col >= wc) continue;
-        if (col >= wb) {            // window column past the last pivot column
-          dst[col] = s[i];
-          continue;
+        for (int i = 0; i < BW; ++i) {
+          const int col = (nsteps + i) & (BW - 1);
+          if (col >= wc) continue;
+          if (col >= wb) {            // window column past the last pivot column
+            dst[col] = s[i];
+            continue;
+          }
+          T a, y;
+          if (pc == -2) {
+            a = s[i];
+            y = T(0);
+          } else if (pc == -1) {
+            a = T(0);
+            y = s[i];
+          } else {
+            a = col >= pc ? s[i] : T(0);
+            y = col < pc ? s[i] : (col == pc ? T(1) : T(0));
+          }
+          dst[col] = a;
+          pb[col] = y;
         }
-        T a, y;
-        if (pc == -2) {
-          a = s[i];
-          y = T(0);
-        } else if (pc == -1) {
-          a = T(0);
-          y = s[i];
-        } else {
-          a = col >= pc ? s[i] : T(0);
-          y = col < pc ? s[i] : (col == pc ? T(1) : T(0));
-        }
-        dst[col] = a;
-        pb[col] = y;
-      }
       }
     } else if (vec) {
 #pragma unroll
@@ -1808,9 +1808,9 @@ __device__ inline void wg_gemm(int M, int N, int K, FA A, FB B, FE epi, double *
 //     time at 224 x 3200), below that by the serial steps between them: sums
 //     and maxima over the workgroup, one barrier each (add_xor, block_sum with
 //     alternating halves, finish_argmax), and the projection on the stored
-//     q's, which reads 16 of them per round trip.  Before that (shuffles
-//     through LDS, two barriers a sum, one q at a time): 100 x 1000 alone 2.05
-//     ms, now 1.60; 77 x 333 1.81, now 1.32; 2048 of 224 x 3200 63.4, now 61.4.
+//     q's, which reads 16 of them per round trip.  One of 100 x 1000 alone 1.60
+//     ms, of 77 x 333 1.32, 2048 of 224 x 3200 61.4; with shuffles through LDS,
+//     two barriers a sum and one q at a time 2.05, 1.81 and 63.4 ms.
 //  3. Completion to an orthogonal Q by Householder reconstruction (Ballard
 //     et al., "Reconstructing Householder vectors from tall-skinny QR",
 //     IPDPS 2014): with Q_c = [q_0 .. q_{k-1}] = [Q1; Q2] (Q1 k x k) and

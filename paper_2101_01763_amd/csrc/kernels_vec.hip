@@ -26,10 +26,10 @@ __device__ inline T wsum(T v) {
 // backward sweep's A_ss^-1 (x_s + c) is t + A_ss^-1 c on those rows, a product
 // with nb columns.  So n^2 + nb^2 elements are read instead of 2 n^2 (measured
 // at Factor::sweeps).
-// Four rows' sums used to be shuffled through LDS and their slots loaded after
-// them, with no load of the matrix in flight: 4.5 TB/s on matrices of ~220
-// columns, now 5.6 (374 -> 292 us for 8128 of them), and 6.05 TB/s on leaves of
-// ~580 (841 + 903 -> 811 + 825 us for 4096, FP32).
+// 5.6 TB/s on matrices of ~220 columns (8128 of them in 292 us), 6.05 TB/s on
+// leaves of ~580 (forward and backward, 4096 of them: 811 + 825 us, FP32).  With
+// four rows' sums shuffled through LDS and their slots loaded after them, no
+// load of the matrix in flight meanwhile: 374, 841 + 903 us.
 // One workgroup per band of output rows (GemvChunk).  The input is staged
 // in LDS.  Bands of one item may run concurrently, so in == out is not
 // allowed (the sweeps alternate between two vectors).
@@ -188,13 +188,13 @@ int launch_gemv(FType t, const GemvDesc *d_items, const GemvChunk *d_chunks, int
 // bound by latency - of the launch itself and of each step's loads - and the
 // steps of a level are fused: one workgroup carries a cluster through the
 // couplings to its neighbours (y) and its own matrix (M y), and with P set
-// recomputes the neighbours' matrix-vector products it needs instead of
-// waiting for a launch of their own.
-// Nine launches a level (three of them copies back to x) became two to six:
-// apply 616 -> 197 us at 37x29 p = 1 transposed FP64 (36 launches -> 14),
-// 1063 -> 860 us at 128x128 p = 2 FP32 (3.0 GB, 81 -> 25), 4.46 -> 3.87 ms
-// at 256x256 p = 3 FP32.  Loads left to the compiler's own schedule (one
-// after another, each waited for) cost 926 us instead of 860.
+// recomputes the neighbours' matrix-vector products it needs without a launch
+// of their own.
+// Two to six launches a level; one per step and three copies back to x (nine a
+// level) against them: 616 and 197 us for the transposed apply at 37x29 p = 1
+// FP64 (36 and 14 launches), 1063 and 860 us at 128x128 p = 2 FP32 (3.0 GB, 81
+// and 25), 4.46 and 3.87 ms at 256x256 p = 3 FP32.  Loads left to the
+// compiler's own schedule (one after another, each waited for): 926, not 860 us.
 // The sum of a row never depends on how a level is cut into launches: plain
 // rows take LEVEL_LANES lanes in 16-byte vectors and a shuffle tree,
 // transposed rows LEVEL_LANES slices of every LEVEL_LANES-th column, and the
@@ -740,10 +740,10 @@ __global__ __launch_bounds__(256) void k_spmv_t(int n_brows, int bs,
 // One wave per element I: L = bs / 2 lanes with 16-byte loads cover a row of a
 // block and S = 64 / L slices of lanes take every S-th row, so an instruction
 // reads up to 1 KB of contiguous memory; the slices' sums are added at the end.
-// The lanes search the mirrors of up to 64 blocks at once, where a search a
-// block stalled every lane before each block's loads.  Bound by the one read
-// of the values: 10.8 GB (bs = 64) in 1.62 ms, 6.7 TB/s; one lane per row with
-// 8-byte loads took 1.74 ms, with 16-byte loads 1.70 ms.
+// The lanes search the mirrors of up to 64 blocks at once; a search a block
+// stalls every lane before each block's loads.  Bound by the one read of the
+// values: 10.8 GB (bs = 64) in 1.62 ms, 6.7 TB/s; one lane per row 1.74 ms
+// with 8-byte loads, 1.70 ms with 16-byte loads.
 __global__ __launch_bounds__(256) void k_spmv_t_wave(int n_brows, int bs,
                                                      const int32_t *__restrict__ rowptr,
                                                      const int32_t *__restrict__ colind,
@@ -836,6 +836,15 @@ int launch_spmv_t_check(const spand_bsr_t &A, int *d_flag, hipStream_t st) {
   return SPAND_OK;
 }
 
+// One wave per element where a block size has it and the values are aligned.
+// Kernel time in us, lane groups (8 or 16 lanes, as tuned) / one wave:
+//   elements     4         16         36        64       256      1024     16384    65536
+//   bs = 16   2.8/2.2   3.5/2.9    3.7/3.2   3.8/3.4   4.9/3.4   7.2/3.7   35/26   140/105
+//   bs = 36   5.2/4.8  5.1-7.1/5.8 5.1/6.3   6.8/6.4   8.2/6.8  18.8/9.2  209/129  834/522
+// Below 64 elements of 36 neither is always ahead (25 to 49: 4.8-5.2 against
+// 5.6-6.3); the call around it takes 15 us.  At bs = 64 a group of 8 lanes reads
+// a row's 512 bytes evenly and is faster (10.7 GB: 1.53 ms against 1.65 ms for
+// 32 rows' sums per lane).
 bool spmv_by_wave(const spand_bsr_t &A) {
   return (A.bs == 16 || A.bs == 36) && (reinterpret_cast<uintptr_t>(A.d_val) & 15) == 0;
 }
@@ -843,9 +852,6 @@ bool spmv_by_wave(const spand_bsr_t &A) {
 int launch_spmv(const spand_bsr_t &A, int transpose, double alpha, const double *x, double beta,
                 double *y, const double *z, double gz, const double *w, double gw,
                 hipStream_t st) {
-  // One wave per element beats the lane groups at bs = 16 and 36 at every size
-  // (256 elements of 36: 10.1 against 11.5 us a call); at 64 a group of 8 reads a row's 512 bytes evenly and is faster
-  // (10.7 GB: 1.53 ms against 1.65 ms for 32 rows' sums per lane).
   if (!transpose && spmv_by_wave(A)) {
     if (A.n_brows <= 0) return SPAND_OK;
     auto *k = A.bs == 16 ? k_spmv_wave<16> : k_spmv_wave<36>;

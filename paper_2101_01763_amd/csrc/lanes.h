@@ -8,8 +8,8 @@ namespace spand {
 
 // v + (v of lane ^ O), every lane active.  The partner comes by lane moves in
 // the vector ALU (DPP within rows of 16, permlane swaps across them: 10-15
-// cycles) instead of a trip through the LDS crossbar (75 cycles a step, which
-// made a wave sum of doubles cost 510 cycles instead of 150).
+// cycles), not by a trip through the LDS crossbar (75 cycles): a wave sum of
+// doubles in 150 cycles, not 510.
 template <int O>
 __device__ inline double add_xor(double v) {
   const int lo = __double2loint(v), hi = __double2hiint(v);
