@@ -129,10 +129,11 @@ int autotune_gemv(FType t, int bs, const std::function<int(int, GemvSet &)> &bui
       return SPAND_OK;
     }
   }
-  // 32 or 64: the interfaces' F_s and B_s of level 0 take the same height, and
-  // bands of 128 rows lose more on such smaller matrices than they can win on
-  // the leaves (measured when the levels above took it too: 148 ms of sweeps
-  // per solve at 4M unknowns against 140-141)
+  // 32 or 64 rows: an apply is the same with either within 1.5% (FP32 192x192
+  // p = 2 1404 and 1425 us, 256x256 p = 3 3.45-3.49 and 3.48 ms, FP64 192x192
+  // p = 2 2336 and 2352 us), so it does not matter that the parts are not what
+  // is timed; 128 rows are 2-6% slower there (1450 us, 3.54 ms, 2486 us) and
+  // within 1% on smaller systems, whose sets take shorter bands anyway
   int best = 64;
   float bt = 1e30f;
   for (int R : {32, 64}) {
